@@ -135,7 +135,8 @@ struct QueryLds {
 // The queries of a key-sketch scan: cast once per (b, g) into LDS.
 template <int DT>
 struct SketchQuery {
-    QueryLds* ql = nullptr;
+    int8_t (*q8c)[kHeadDim] = nullptr;   // the casts and their exponents in LDS
+    int* eqc = nullptr;
     int q_tag = -1;
 
     // The raw query words of the group's first heads (wave w: heads w and
@@ -166,11 +167,11 @@ struct SketchQuery {
         const int e = sketch_exponent<127>(wave_max(fmaxf(fabsf(x0), fabsf(x1))));
         const uint32_t c2 =
             ((uint32_t)sketch_code<127>(x0, e) & 0xffu) | (((uint32_t)sketch_code<127>(x1, e) & 0xffu) << 8);
-        *reinterpret_cast<uint16_t*>(&ql->q8[h][2 * lane]) = (uint16_t)c2;
-        if (lane == 0) ql->eq[h] = e;
+        *reinterpret_cast<uint16_t*>(&q8c[h][2 * lane]) = (uint16_t)c2;
+        if (lane == 0) eqc[h] = e;
     }
 
-    // Casts the G queries of group (b, g) into ql; wave w takes heads w, w+4, ...
+    // Casts the G queries of group (b, g) into LDS; wave w takes heads w, w+4, ...
     // (the first kQPre of them from group_query_fetch).  Called by every wave;
     // the caller orders it with a barrier before the reads.
     __device__ __forceinline__ void group_query(const ScoreArgs& a, int b, int g, int w, int lane)
@@ -193,7 +194,8 @@ struct KeysSketch : SketchQuery<DT> {
     static constexpr bool kMfmaSplit = false;
     static constexpr int kRowBytes = kHeadDim * BITS / 8;
     using Codes = typename std::conditional<BITS == 8, uint4, uint2>::type;
-    using SketchQuery<DT>::ql;
+    using SketchQuery<DT>::q8c;
+    using SketchQuery<DT>::eqc;
     using SketchQuery<DT>::q_tag;
     Codes kr[kSlots][kRowsPerLane];
     uint32_t ek4[kSlots];   // exponents of the 4 rows, one byte each
@@ -227,8 +229,8 @@ struct KeysSketch : SketchQuery<DT> {
         if (tag == q_tag) return;
 #pragma unroll
         for (int hh = 0; hh < GC; ++hh) {
-            q8[hh] = *reinterpret_cast<const uint4*>(&ql->q8[hc + hh][16 * l8]);
-            eq[hh] = ql->eq[hc + hh];
+            q8[hh] = *reinterpret_cast<const uint4*>(&q8c[hc + hh][16 * l8]);
+            eq[hh] = eqc[hc + hh];
             if constexpr (BITS == 4) {
                 const int ones = 0x01010101;
                 int sq = __builtin_amdgcn_sdot4((int)q8[hh].x, ones, 0, false);
@@ -238,7 +240,7 @@ struct KeysSketch : SketchQuery<DT> {
                 qbias[hh] = 8 * sq;
             }
         }
-        eq_lane = ql->eq[hc + (l8 < GC ? l8 : 0)];   // from LDS: a register-array pick would be indexed
+        eq_lane = eqc[hc + (l8 < GC ? l8 : 0)];   // from LDS: a register-array pick would be indexed
         q_tag = tag;
     }
 
@@ -387,7 +389,8 @@ struct KeysSketchMfma8 : SketchQuery<DT> {
     static constexpr bool kGroupQuery = true;
     static constexpr bool kIntDot = true;
     static constexpr bool kMfmaSplit = true;
-    using SketchQuery<DT>::ql;
+    using SketchQuery<DT>::q8c;
+    using SketchQuery<DT>::eqc;
     using SketchQuery<DT>::q_tag;
     uint4 kr[kSlots][4];       // [tile][group]: the lane's 16 code bytes
     uint32_t ek4[kSlots];      // exponents of the lane's 4 output tokens
@@ -421,8 +424,8 @@ struct KeysSketchMfma8 : SketchQuery<DT> {
         uint4 x = make_uint4(0u, 0u, 0u, 0u);
         eq_lane = 0;
         if (h < a.G) {
-            x = *reinterpret_cast<const uint4*>(&ql->q8[h][(2 * (lane >> 4) + (col & 1)) * 16]);
-            eq_lane = ql->eq[h];
+            x = *reinterpret_cast<const uint4*>(&q8c[h][(2 * (lane >> 4) + (col & 1)) * 16]);
+            eq_lane = eqc[h];
         }
         qb[0] = (uint64_t)x.x | ((uint64_t)x.y << 32);
         qb[1] = (uint64_t)x.z | ((uint64_t)x.w << 32);
@@ -471,7 +474,8 @@ struct KeysSketchMfma4 : SketchQuery<DT> {
     static constexpr bool kIntDot = true;
     static constexpr bool kMfmaSplit = true;
     static constexpr int kRowBytes = kHeadDim / 2;
-    using SketchQuery<DT>::ql;
+    using SketchQuery<DT>::q8c;
+    using SketchQuery<DT>::eqc;
     using SketchQuery<DT>::q_tag;
     uint2 kr[kSlots][4];       // [tile][group]: the lane's 8 code bytes (two words)
     uint32_t ek4[kSlots];      // exponents of the lane's 4 output tokens
@@ -505,8 +509,8 @@ struct KeysSketchMfma4 : SketchQuery<DT> {
         eq_lane = 0;
         if (h < a.G) {
             // codes of the lane's key bytes: 2 per byte, at 2 * (16p' + 8(c & 1) + 32(c >> 1))
-            x = *reinterpret_cast<const uint4*>(&ql->q8[h][32 * (col & 1) + 16 * (qc & 1) + 64 * (qc >> 1)]);
-            eq_lane = ql->eq[h];
+            x = *reinterpret_cast<const uint4*>(&q8c[h][32 * (col & 1) + 16 * (qc & 1) + 64 * (qc >> 1)]);
+            eq_lane = eqc[h];
         }
         qb[0] = (uint64_t)x.x | ((uint64_t)x.y << 32);
         qb[1] = (uint64_t)x.z | ((uint64_t)x.w << 32);
@@ -752,7 +756,8 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(ScoreArgs a)
             ks.template load<0>(a, c0, rg, l8);
             ks.template load<1>(a, c1, rg, l8);
             if (fresh) {
-                ks.ql = &qlds;
+                ks.q8c = qlds.q8;
+                ks.eqc = qlds.eq;
                 ks.group_query(a, bg / a.Hkv, bg % a.Hkv, wv, lane);
                 __syncthreads();
                 cur_bg = bg;
@@ -793,6 +798,287 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(ScoreArgs a)
     }
 }
 
+// ------------------------------------------------------------ long launches --
+//
+// score_units: the matrix-core scans of launches long enough to keep every
+// wave busy with whole 256-token units (use_units below).  Every wave walks
+// its own units, without barriers: kDepth - 1 tiles of keys are always requested ahead (into the
+// next unit as well), the unit's softmax pair is merged in registers, and its
+// logits are collected in LDS and stored when the unit is complete, 1 KiB per
+// head in one instruction, written through to memory.  What bounds such a
+// launch is HBM with reads and writes mixed: 1 GiB of keys alone takes 164 us
+// here (160 us for a bare read), and the 64 MiB of logits cost another 41 us
+// as 128-byte stores left to L2, 37 us written through (sc1) and 30 us as
+// whole units written through; units of 512 tokens (twice the LDS) were
+// slower again (33 us).  One contiguous range of units per wave instead of
+// strided ones: 205 against 194 us.
+
+// Max and sum over lanes l, l ^ 16, l ^ 32, l ^ 48 by row swaps on the vector
+// unit (the LDS exchange of __shfl_xor takes a round trip each).
+__device__ __forceinline__ float max_x16_x32(float v)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+__device__ __forceinline__ float sum_x16_x32(float v)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+constexpr int kUnitTokens = kUnitTiles * kScoreTile;
+constexpr int kAuxNt = 2;    // buffer cache policy: non-temporal
+constexpr int kAuxSc1 = 16;  // buffer cache policy: device scope, i.e. stores written through
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+
+// Key sources of score_units: the operands of KeysF16Mfma / KeysSketchMfma8 /
+// KeysSketchMfma4 loaded through buffer descriptors of the (b, g) rows [0, n),
+// so that rows past n read as zeros without a test and a tile's addresses are
+// one lane offset plus immediates.  group(): the next loads' (b, g).
+// query(): the queries of a (b, g), at most kMfmaHeads heads.
+
+template <int DT>
+struct UnitKeysF16 : KeysF16Mfma<DT> {
+    static constexpr int kDepth = 2;    // tiles in registers
+    static constexpr bool kCast = false;
+    using KeysF16Mfma<DT>::qb;
+    uint4 ks[kDepth][8];
+    __amdgpu_buffer_rsrc_t rs;
+    uint32_t loff, sn2;
+
+    __device__ __forceinline__ void init(const ScoreArgs& a, int lane)
+    {
+        const int i = lane & 15, q = i >> 2, u = (i >> 1) & 1, p = i & 1;
+        sn2 = (uint32_t)(a.k_sn * 2);
+        loff = (uint32_t)(8 * q + 4 * u) * sn2 + (uint32_t)(2 * (lane >> 4) + p) * 16u;
+    }
+
+    __device__ __forceinline__ void group(const ScoreArgs& a, int b, int g)
+    {
+        rs = make_rsrc(a.k + (int64_t)b * a.k_sb + (int64_t)g * a.k_sh, (uint32_t)(a.n - 1) * sn2 + 2u * kHeadDim);
+    }
+
+    template <int SLOT>
+    __device__ __forceinline__ void fetch(int j0)
+    {
+        const uint32_t t = loff + (uint32_t)j0 * sn2;
+#pragma unroll
+        for (int gr = 0; gr < 4; ++gr)
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                ks[SLOT][2 * gr + s] = __builtin_bit_cast(
+                    uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(t + (uint32_t)gr * sn2 + 128u * s), 0, kAuxNt));
+    }
+
+    __device__ __forceinline__ void query(const ScoreArgs& a, const TileCoord& c, int lane)
+    {
+        this->mquery(a, c, 0, lane);
+    }
+
+    template <int SLOT>
+    __device__ __forceinline__ void logits(int lane, float (&out)[4])
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) this->kr[0][i] = ks[SLOT][i];
+        this->template dots<0>(lane, out);
+    }
+};
+
+// The sketch sources: KEYS = KeysSketchMfma8<DT> or KeysSketchMfma4<DT>, whose
+// group's queries are cast into the wave's own LDS.
+template <int DT, typename KEYS, int BITS>
+struct UnitKeysSketch : KEYS {
+    static constexpr int kDepth = 4;
+    static constexpr bool kCast = true;
+    static constexpr int kRowBytes = kHeadDim * BITS / 8;
+    using Codes = typename std::conditional<BITS == 8, uint4, uint2>::type;
+    Codes ks[kDepth][4];
+    uint32_t es[kDepth];
+    __amdgpu_buffer_rsrc_t rs, re;
+    uint32_t loff, eoff;
+    int qb_b = -1, qb_g = -1;   // whose queries are held
+
+    __device__ __forceinline__ void init(const ScoreArgs&, int lane)
+    {
+        const int i = lane & 15, q = i >> 2, u = (i >> 1) & 1, p = i & 1, qc = lane >> 4;
+        if constexpr (BITS == 8) loff = (uint32_t)((8 * q + 4 * u) * kRowBytes + (2 * qc + p) * 16);
+        else loff = (uint32_t)((8 * q + u) * kRowBytes + 16 * p + 8 * (qc & 1) + 32 * (qc >> 1));
+        eoff = (uint32_t)(8 * qc + 4 * (lane & 1));
+    }
+
+    __device__ __forceinline__ void group(const ScoreArgs& a, int b, int g)
+    {
+        const int64_t bg = (int64_t)b * a.Hkv + g;
+        rs = make_rsrc(a.k8 + bg * a.cap * kRowBytes, (uint32_t)a.n * kRowBytes);
+        re = make_rsrc(a.k_exp + bg * a.cap, (uint32_t)(a.n + 3) & ~3u);   // cap is a multiple of 4
+    }
+
+    template <int SLOT>
+    __device__ __forceinline__ void fetch(int j0)
+    {
+        const uint32_t t = loff + (uint32_t)j0 * kRowBytes;
+        constexpr uint32_t kStep = (BITS == 8 ? 1 : 2) * kRowBytes;   // a group's next token (KeysSketchMfma8 / 4)
+#pragma unroll
+        for (int gr = 0; gr < 4; ++gr) {
+            if constexpr (BITS == 8)
+                ks[SLOT][gr] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(t + gr * kStep), 0, kAuxNt));
+            else
+                ks[SLOT][gr] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(t + gr * kStep), 0, kAuxNt));
+        }
+        es[SLOT] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(re, (int)(eoff + (uint32_t)j0), 0, 0);
+    }
+
+    // Casts the group's queries (at most kMfmaHeads heads) into the wave's own
+    // LDS and reads the lane's operands back.
+    __device__ __forceinline__ void query(const ScoreArgs& a, const TileCoord& c, int lane)
+    {
+        if (c.b == qb_b && c.g == qb_g) return;
+        qb_b = c.b;
+        qb_g = c.g;
+        uint32_t word[kMfmaHeads];
+#pragma unroll
+        for (int h = 0; h < kMfmaHeads; ++h) word[h] = *this->qword(a, c.b, c.g, min(h, a.G - 1), lane);
+#pragma unroll
+        for (int h = 0; h < kMfmaHeads; ++h)
+            if (h < a.G) this->cast_head(word[h], h, lane);
+        // the wave's own LDS, written and read by it alone: in order, once the compiler keeps the order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        this->q_tag = -1;
+        this->mquery(a, c, 0, lane);
+    }
+
+    template <int SLOT>
+    __device__ __forceinline__ void logits(int lane, float (&out)[4])
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) this->kr[0][i] = ks[SLOT][i];
+        this->ek4[0] = es[SLOT];
+        this->template dots<0>(lane, out);
+    }
+};
+
+// One wave-tile: compute_tile_mfma16 (the same sums in the same order) with
+// at most kMfmaHeads heads; the logits go to the unit's LDS rows (unit[head][token]), the pair is returned.
+template <int SLOT, typename Keys>
+__device__ __forceinline__ void compute_unit_tile(const ScoreArgs& a, int j0, int i0, int lane, bool live, Keys& ks,
+                                                  float* urow, float& mo, float& zo)
+{
+    const int jl = 8 * (lane >> 4) + 4 * (lane & 1);   // this lane's first token in the tile
+    const int left = a.n - j0 - jl;
+    float mine[4], x[4];
+    ks.template logits<SLOT>(lane, mine);
+    float m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        x[i] = i < left ? a.s2 * mine[i] : -INFINITY;
+        m = fmaxf(m, x[i]);
+    }
+    if (live) *reinterpret_cast<float4*>(urow + i0 + jl) = make_float4(mine[0], mine[1], mine[2], mine[3]);
+    m = max_x16_x32(fmaxf(m, dpp<0xB1>(m)));
+    float z = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z += i < left ? exp2_ftz(x[i] - m) : 0.0f;
+    z += dpp<0xB1>(z);
+    mo = m;
+    zo = sum_x16_x32(z);
+}
+
+// HB: heads that the unit buffer holds (4 or kMfmaHeads, at least G).
+template <typename Keys, int HB>
+__global__ __launch_bounds__(256, 4) void score_units_kernel(ScoreArgs a)
+{
+    __shared__ float unit_lds[4][HB][kUnitTokens];
+    __shared__ typename std::conditional<Keys::kCast, int8_t[4][HB][kHeadDim], int>::type q8_lds;
+    __shared__ int eq_lds[4][HB];
+    constexpr int kD = Keys::kDepth;
+    static_assert(kUnitTiles % kD == 0 && kUnitTokens == 4 * 64, "slots repeat per unit; 16 bytes per lane and head");
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (a.zero_ptr) {
+        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.zero_words; i += (int64_t)gridDim.x * 256)
+            a.zero_ptr[i] = 0u;
+    }
+    const int total = a.B * a.Hkv * a.npart, nw = gridDim.x * 4;
+    int u = blockIdx.x * 4 + wv;   // then u + nw, ...: neighbours in memory are read at about the same time
+    if (u >= total) return;
+    Keys ks;
+    ks.init(a, lane);
+    if constexpr (Keys::kCast) {
+        ks.q8c = q8_lds[wv];
+        ks.eqc = eq_lds[wv];
+    }
+    const int h = (lane & 15) >> 1;
+    const bool live = h < a.G;
+    float* urow = unit_lds[wv][live ? h : 0];
+    int bg = u / a.npart, unit = u % a.npart;
+    ks.group(a, bg / a.Hkv, bg % a.Hkv);
+    {
+        const int j0 = unit * kUnitTokens;
+        ks.template fetch<0>(j0);
+        if constexpr (kD > 2) {
+            ks.template fetch<1>(j0 + kScoreTile);
+            ks.template fetch<2>(j0 + 2 * kScoreTile);
+        }
+    }
+    for (;;) {
+        const int j0 = unit * kUnitTokens;
+        TileCoord c;
+        c.b = bg / a.Hkv;
+        c.g = bg % a.Hkv;
+        ks.query(a, c, lane);
+        const bool more = u + nw < total;
+        const int un = more ? u + nw : u;   // the last unit's look-ahead reads its own first tiles again
+        const int bgn = un / a.npart, jn = (un % a.npart) * kUnitTokens;
+        float mt[kUnitTiles], zt[kUnitTiles];
+        auto tile = [&](auto ic) {   // a compile-time tile number: register slots must not be indexed
+            constexpr int i = decltype(ic)::value;
+            constexpr int p = i + kD - 1;   // the tile requested now
+            if constexpr (p == kUnitTiles) ks.group(a, bgn / a.Hkv, bgn % a.Hkv);
+            ks.template fetch<p % kD>(p < kUnitTiles ? j0 + p * kScoreTile : jn + (p - kUnitTiles) * kScoreTile);
+            compute_unit_tile<i % kD>(a, j0 + i * kScoreTile, i * kScoreTile, lane, live, ks, urow, mt[i], zt[i]);
+        };
+        tile(std::integral_constant<int, 0>{});
+        tile(std::integral_constant<int, 1>{});
+        tile(std::integral_constant<int, 2>{});
+        tile(std::integral_constant<int, 3>{});
+        tile(std::integral_constant<int, 4>{});
+        tile(std::integral_constant<int, 5>{});
+        tile(std::integral_constant<int, 6>{});
+        tile(std::integral_constant<int, 7>{});
+        // the unit's logits, one row of 1 KiB per head (the wave's own LDS, in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int jr = j0 + 4 * lane;
+        const __amdgpu_buffer_rsrc_t rl =
+            make_rsrc(a.logits + ((int64_t)c.b * a.Hq + c.g * a.G) * a.ld, (uint32_t)a.G * (uint32_t)a.ld * 4u);
+        for (int hh = 0; hh < a.G; ++hh) {
+            const u32x4_t v = *reinterpret_cast<const u32x4_t*>(&unit_lds[wv][hh][4 * lane]);
+            if (jr < a.ld)   // rows are padded to ld, a multiple of 4
+                __builtin_amdgcn_raw_buffer_store_b128(v, rl, (int)((uint32_t)hh * (uint32_t)a.ld * 4u + 4u * (uint32_t)jr), 0, kAuxSc1);
+        }
+        float m = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < kUnitTiles; ++i) m = fmaxf(m, mt[i]);
+        float z = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kUnitTiles; ++i) z += mt[i] == -INFINITY ? 0.0f : zt[i] * exp2_ftz(mt[i] - m);
+        if (lane < 16 && !(lane & 1) && live)
+            a.part[((int64_t)c.b * a.Hq + c.g * a.G + h) * a.npart + unit] = make_float2(m, z);
+        if (!more) break;
+        u = un;
+        bg = bgn;
+        unit = un % a.npart;
+    }
+}
+
 // Workgroups of `kernel` that stay resident on one CU (queried once per instantiation).
 template <typename K>
 int resident_per_cu(K kernel)
@@ -805,12 +1091,51 @@ int resident_per_cu(K kernel)
     return v;
 }
 
+// Whether a matrix-core scan of ATTN logits runs as score_units (whole units
+// per wave) instead of score_tiles (a unit per workgroup).  Measured (us,
+// score_tiles -> score_units; GQA 32/8 unless said):
+//   16-bit keys, from 16 units per CU on, i.e. one for every resident wave
+//     (4096 here): 1 x 131K 55.6 -> 51.2, 8 x 32K 110 -> 94, 32 x 32K 425 ->
+//     393; below that too few waves have work: 1 x 64K 25.9 -> 27.3, 3 x 32K
+//     even; G < 4: the vector form's dot chains are short (8 x 4K MHA 45 ->
+//     50, 2 x 32K MHA 92 -> 94)
+//   int8 sketch, the same line: 4 x 32K 34.7 -> 31.9, 4 x 131K 133 -> 105,
+//     3 x 32K 25 -> 26, MHA 8 x 4K 28 -> 33
+//   int4 sketch, from half of that and for every G up to 8 (half the bytes to
+//     keep in flight, and unpacking codes costs the vector form more): 2 x 32K
+//     14.2 -> 12.7, 4 x 32K 27.6 -> 20.0, 4 x 131K 94 -> 61, MHA 8 x 4K 23.5
+//     -> 20.5; 1 x 32K 9.5 -> 9.9
+// The descriptor's offsets are 32 bits: key rows up to two units past n must
+// lie below 4 GiB from the first.
+inline bool use_units(const ScoreArgs& a, int64_t total, int ncu)
+{
+    if (a.G > kMfmaHeads) return false;
+    if (a.k8) return a.kbits == 4 ? total >= 8ll * ncu : a.G >= 4 && total >= 16ll * ncu;
+    return a.G >= 4 && total >= 16ll * ncu && ((int64_t)a.n + 2 * kUnitTokens) * a.k_sn * 2 < (1ll << 32);
+}
+
+template <typename Keys>
+hipError_t launch_units(const ScoreArgs& a, int64_t total, int ncu, hipStream_t st, Stamp ts)
+{
+    auto go = [&](auto kernel) {
+        const int64_t cap = (int64_t)ncu * resident_per_cu(kernel), want = (total + 3) / 4;
+        hipExtLaunchKernelGGL(kernel, dim3((unsigned)(want < cap ? want : cap)), dim3(256), 0, st, ts.start, ts.stop, 0, a);
+        return hipGetLastError();
+    };
+    return a.G <= 4 ? go(score_units_kernel<Keys, 4>) : go(score_units_kernel<Keys, kMfmaHeads>);
+}
+
 // Persistent grid: every workgroup resident at once, each with at least one unit.
 template <int DT, int GC, int OUT>
 hipError_t launch_score_inst(const ScoreArgs& a, int ncu, hipStream_t st, Stamp ts)
 {
     const int64_t total = (int64_t)a.B * a.Hkv * a.npart;
     if constexpr (OUT == kOutLogits) {
+        if (use_units(a, total, ncu)) {
+            if (a.k8 && a.kbits == 4) return launch_units<UnitKeysSketch<DT, KeysSketchMfma4<DT>, 4>>(a, total, ncu, st, ts);
+            if (a.k8) return launch_units<UnitKeysSketch<DT, KeysSketchMfma8<DT>, 8>>(a, total, ncu, st, ts);
+            return launch_units<UnitKeysF16<DT>>(a, total, ncu, st, ts);
+        }
         // int4 sketch, ATTN logits, G >= 4: integer dots on the matrix cores (with fewer heads per
         // key the vector units' dot chains are short and faster)
         if (a.k8 && a.kbits == 4 && a.G >= 4) {
