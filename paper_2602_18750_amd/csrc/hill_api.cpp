@@ -269,6 +269,15 @@ hill_status check_sketch(const Shape& s, const int8_t* k8, const int8_t* k_exp, 
     return HILL_OK;
 }
 
+// Parts of the first-digit histogram that the importance update of a step
+// with a refine pass counts into (in the place of the selected lists).
+int step_hist_parts(const Shape& s)
+{
+    const int64_t nup = (s.n + kUpdChunk - 1) / kUpdChunk;
+    const int per = update_chunks_per_wg((int64_t)s.B * s.R * nup);
+    return hist_parts((nup + per - 1) / per, s.n);
+}
+
 // Scoring; if `hist` is given the first selection digit is counted as a side
 // effect (hill_step) and the counts are cleared by the first kernel.
 hill_status run_score(const hill_desc* d, const Shape& s, const Layout& L, const void* q, const void* k,
@@ -277,7 +286,12 @@ hill_status run_score(const hill_desc* d, const Shape& s, const Layout& L, const
 {
     const Stamp scan = stage(ev, HILL_STAGE_SCAN);
     const Stamp upd = stage(ev, HILL_STAGE_UPDATE);
-    uint32_t* hist = with_hist ? at<uint32_t>(ws, L.hist1) : nullptr;
+    // Where the update counts first digits: for a streamed selection (which counts them only without a
+    // bound) one histogram per row, for the refine pass as many parts as hist_parts says.
+    const int64_t nup = (s.n + kUpdChunk - 1) / kUpdChunk, rows = (int64_t)s.B * s.R;
+    const int upd_per = s.mode == HILL_SCORE_ATTN ? update_chunks_per_wg(rows * nup) : 1;
+    const int parts = stream_prev || s.mode == HILL_SCORE_RAW ? 1 : step_hist_parts(s);
+    uint32_t* hist = with_hist ? at<uint32_t>(ws, parts > 1 ? L.sel_list : L.hist1) : nullptr;
     ScoreArgs a{};
     a.q = static_cast<const uint16_t*>(q);
     a.k = static_cast<const uint16_t*>(k);
@@ -300,6 +314,10 @@ hill_status run_score(const hill_desc* d, const Shape& s, const Layout& L, const
     a.s_sr = d->s_stride_r;
     a.zero_ptr = with_hist ? at<uint32_t>(ws, L.zero) : nullptr;
     a.zero_words = with_hist ? (stream_prev ? L.zero_words_stream : L.zero_words) : 0;
+    if (with_hist && parts > 1) {
+        a.zero2_ptr = hist;
+        a.zero2_words = rows * parts * kHistRow;
+    }
     a.k8 = sk.k8;
     a.k_exp = sk.k_exp;
     a.cap = sk.cap;
@@ -323,6 +341,7 @@ hill_status run_score(const hill_desc* d, const Shape& s, const Layout& L, const
     u.ld = s.ld;
     u.s2 = a.s2;
     u.hist = hist;
+    u.hist_reps = parts;
     u.pin_lo = s.pin_lo;
     u.pin_hi = s.pin_hi;
     if (stream_prev) {   // streamed selection (ATTN only): candidate pairs above the previous threshold
@@ -343,8 +362,8 @@ hill_status run_score(const hill_desc* d, const Shape& s, const Layout& L, const
         u.tph = kUpdThreads / (s.R == 1 ? s.Hq : s.G);   // heads per row <= 256 (validated)
         u.inv_tph = 1.0f / (float)u.tph;
         u.stats = nullptr;
-        const int64_t update_blocks = (int64_t)s.B * s.R * ((s.n + kUpdChunk - 1) / kUpdChunk);
-        if (!update_reduces_stats(s.R == 1 ? s.Hq : s.G, s.npart, update_blocks)) {
+        u.per = upd_per;
+        if (!update_reduces_stats(s.R == 1 ? s.Hq : s.G, s.npart, rows * ((nup + u.per - 1) / u.per))) {
             float2* stats = at<float2>(ws, L.stats);
             HIP_TRY(launch_softmax_stats(a.part, stats, s.B * s.Hq, s.npart, st, stage(ev, HILL_STAGE_STATS)));
             u.stats = stats;
@@ -376,6 +395,7 @@ RefineArgs refine_args(const hill_desc* d, const Shape& s, const Layout& L, cons
     r.k = ksel;
     r.nchunks = L.nchunks;
     r.hist1 = at<uint32_t>(ws, L.hist1);
+    r.hist_reps = 1;
     r.hist2 = at<uint32_t>(ws, L.hist2);
     r.cand_key = at<uint32_t>(ws, L.cand_key);
     r.cand_n = at<uint32_t>(ws, L.cand_n);
@@ -552,6 +572,10 @@ hill_status run_step(const hill_desc* d, const void* q, const void* k, const voi
         HIP_TRY(launch_topk_emit_attn_stream(r, a, s.dtype, st, stage(e, HILL_STAGE_SELECT)));
     } else {
         r.state_out = state4;   // NULL, or a reset step's fresh bound
+        if (s.mode == HILL_SCORE_ATTN && step_hist_parts(s) > 1) {   // as run_score counted it
+            r.hist_reps = step_hist_parts(s);
+            r.hist1 = reinterpret_cast<const uint32_t*>(r.sel_list);
+        }
         HIP_TRY(launch_topk_refine(r, s.B * s.R, st, stage(e, HILL_STAGE_REFINE)));
         HIP_TRY(launch_topk_emit_attn(r, a, s.dtype, st, stage(e, HILL_STAGE_SELECT)));
     }
@@ -753,6 +777,7 @@ hill_status hill_bkp_update(const hill_bkp_desc* d, const int32_t* idx, int32_t 
         r.k = a.f;
         r.nchunks = L.nchunks;
         r.hist1 = at<uint32_t>(ws, L.hist1);
+        r.hist_reps = 1;
         r.hist2 = at<uint32_t>(ws, L.hist2);
         r.cand_key = at<uint32_t>(ws, L.cand_key);
         r.cand_n = at<uint32_t>(ws, L.cand_n);

@@ -42,6 +42,8 @@ struct ScoreArgs {
     int64_t s_sb, s_sr;
     uint32_t* zero_ptr;      // nullable: words to clear for a later kernel
     int64_t zero_words;
+    uint32_t* zero2_ptr;     // the same, a second range
+    int64_t zero2_words;
     const int8_t* k8;        // nullable: key sketch scored instead of k: int8 codes [B,Hkv,cap,128]
                              //   (kbits 8) or packed int4 codes [B,Hkv,cap,64] bytes (kbits 4)
     const int8_t* k_exp;     //   its per-row exponents [B,Hkv,cap]
@@ -73,14 +75,15 @@ struct UpdateArgs {
     const float2* stats;     // ATTN: [B,Hq] (max, 1/sum) in the exp2 domain, or null: then
     const float2* part;      //   the kernel reduces the [B,Hq,npart] unit partials itself
     int npart;
+    int per;                 // update_attn: consecutive kUpdChunk-token chunks per workgroup
     int tph;                 // update_attn: threads per head in the reduction (kUpdThreads / heads per row)
     float inv_tph;           //   and 1 / tph
     float* s;
     int64_t s_sb, s_sr;
     int B, Hq, Hkv, G, R, n;
     float s2;
-    uint32_t* hist;          // nullable: [B*R, kHistRow] first-digit counts (fine, coarse); with a
-                             // streamed bound only keys in the bound's bin or above are counted
+    uint32_t* hist;          // nullable: [B*R, hist_reps, kHistRow] first-digit counts (fine, coarse) in
+    int hist_reps;           //   hist_reps parts, workgroup i counting into part i % hist_reps
     int pin_lo, pin_hi;      // tokens outside [pin_lo, pin_hi) count with the largest key (lo == hi: all)
     // streamed selection (nullable prev): candidates above the previous step's threshold
     const uint4* prev;       // [B*R, 2] caller's state (see StreamState)
@@ -156,7 +159,8 @@ struct RefineArgs {
     const float* s;
     int64_t s_sb, s_sr;
     int R, n, k, nchunks;
-    const uint32_t* hist1;   // [rows, kHistRow] first-digit counts (bits 31..20; coarse: bits 31..26)
+    const uint32_t* hist1;   // [rows, hist_reps, kHistRow] first-digit counts (bits 31..20; coarse: bits 31..26)
+    int hist_reps;           //   in hist_reps parts to be added (refine pass; 1 where no refine pass runs)
     uint32_t* hist2;         // [rows, kHistRow] second-digit counts (bits 19..8; coarse: bits 19..14), zeroed before
     uint32_t* cand_key;      // [rows, n] keys inside the first-digit bin, chunk c at offset c*kSelChunk
     uint32_t* cand_n;        // [rows, nchunks]
@@ -256,19 +260,50 @@ hipError_t launch_bkp_lists(const BkpArgs& a, int rows, hipStream_t st);
 hipError_t launch_score_tiles(const ScoreArgs& a, int dtype, ScoreOut out, int ncu, hipStream_t st, Stamp ts = {});
 hipError_t launch_softmax_stats(const float2* part, float2* stats, int bh, int npart, hipStream_t st,
                                 Stamp ts = {});
+// Chunks of kUpdChunk tokens per update_attn workgroup: one until the row
+// blocks exceed the kUpdResident workgroups that run at once (4 per CU of 256),
+// then as many as keep the grid there, so that the statistics, the histogram's
+// clear and flush and the launch of a workgroup are paid once for several
+// chunks.  A pure function of the shape (the workspace layout depends on it).
+constexpr int kUpdResident = 4 * 256;
+constexpr int kUpdMaxChunks = 16;
+inline int update_chunks_per_wg(int64_t blocks)
+{
+    const int64_t per = (blocks + kUpdResident - 1) / kUpdResident;
+    return per < 1 ? 1 : per > kUpdMaxChunks ? kUpdMaxChunks : (int)per;
+}
+
+// Parts of a row's first-digit histogram: S values cluster in a few dozen
+// bins, so every workgroup's flush adds to the same few cache lines, about 3
+// ns per request one after another; past some workgroups per row they are
+// spread over several copies, which the refine pass adds.  update_attn at 1 x
+// 131K (1024 workgroups on a row) in us: one part 18.2, two 11.4, four 8.7,
+// eight 6.9; 1 x 32K (256) 8.6, 6.3, 5.0; 79 workgroups on a row: even.  The
+// refine pass's second round trip costs 0.2 us at most.  The copies take the
+// place of the row's list of selected tokens (4 bytes per token, written after
+// the refine pass): at most `room` of them.
+constexpr int kMaxHistParts = 8;
+inline int hist_parts(int64_t wgs_per_row, int n)
+{
+    const int64_t room = (int64_t)n * sizeof(int32_t) / (kHistRow * sizeof(uint32_t));
+    int r = 1;
+    while (r < kMaxHistParts && 2 * r <= room && wgs_per_row > 32 * r) r *= 2;
+    return r;
+}
+
 // Whether update_attn reduces the softmax partials itself (no separate
 // softmax_stats launch): every thread then loads at most kStatLoads of them,
-// and every update workgroup re-reads its row's partials. The extra launch
-// costs about 4 us; the re-reads it saves cost about 0.05 us per MiB (8 x 32K
-// tokens, 64 MiB: about 3 us; 32 x 32K, 256 MiB: about 12.5 us), so calls
-// re-reading more than kStatRereadMax bytes take the separate launch.
+// and every update workgroup (of one or more chunks) re-reads its row's
+// partials. The extra launch costs about 5 us; the re-reads it saves cost
+// about 0.05 us per MiB, so calls re-reading more than kStatRereadMax bytes
+// take the separate launch.
 constexpr int64_t kStatRereadMax = 128ll << 20;
-inline bool update_reduces_stats(int nheads_per_row, int npart, int64_t update_blocks)
+inline bool update_reduces_stats(int nheads_per_row, int npart, int64_t update_wgs)
 {
     if (nheads_per_row < 1 || nheads_per_row > 256) return false;
     const int tph = kUpdThreads / nheads_per_row;
     return (int64_t)npart <= (int64_t)kStatLoads * tph &&
-           update_blocks * npart * nheads_per_row * (int64_t)sizeof(float2) <= kStatRereadMax;
+           update_wgs * npart * nheads_per_row * (int64_t)sizeof(float2) <= kStatRereadMax;
 }
 hipError_t launch_update_attn(const UpdateArgs& a, hipStream_t st, Stamp ts = {});
 hipError_t launch_update_raw_groups(const UpdateArgs& a, hipStream_t st, Stamp ts = {});

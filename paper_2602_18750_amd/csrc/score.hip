@@ -41,6 +41,16 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* p, int64_t wor
         p[i] = 0u;
 }
 
+// The words that a later kernel counts into.
+__device__ __forceinline__ void clear_words(const ScoreArgs& a)
+{
+    const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    if (a.zero_ptr)
+        for (int64_t i = i0; i < a.zero_words; i += step) a.zero_ptr[i] = 0u;
+    if (a.zero2_ptr)
+        for (int64_t i = i0; i < a.zero2_words; i += step) a.zero2_ptr[i] = 0u;
+}
+
 struct TileCoord {
     int b, g, tile, j0;
 };
@@ -722,10 +732,7 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(ScoreArgs a)
     const int rg = lane >> 3;
     const int l8 = lane & 7;
 
-    if (a.zero_ptr) {
-        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.zero_words; i += (int64_t)gridDim.x * 256)
-            a.zero_ptr[i] = 0u;
-    }
+    clear_words(a);
 
     const int total = a.B * a.Hkv * a.npart;
     const int per = (total + gridDim.x - 1) / gridDim.x;
@@ -1003,10 +1010,7 @@ __global__ __launch_bounds__(256, 4) void score_units_kernel(ScoreArgs a)
     static_assert(kUnitTiles % kD == 0 && kUnitTokens == 4 * 64, "slots repeat per unit; 16 bytes per lane and head");
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (a.zero_ptr) {
-        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.zero_words; i += (int64_t)gridDim.x * 256)
-            a.zero_ptr[i] = 0u;
-    }
+    clear_words(a);
     const int total = a.B * a.Hkv * a.npart, nw = gridDim.x * 4;
     int u = blockIdx.x * 4 + wv;   // then u + nw, ...: neighbours in memory are read at about the same time
     if (u >= total) return;

@@ -284,6 +284,34 @@ __device__ __forceinline__ void find_digit(const DigitHist& d, uint32_t need, ui
     }
 }
 
+// find_digit over a histogram in `parts` copies of a row: the coarse bins of
+// all copies in one round trip, then the 64 fine bins of the chosen coarse bin
+// in another (loading every copy whole would cost more than that round trip).
+// Every wave finds the same; the first publishes.
+__device__ __forceinline__ void find_digit_parts(const uint32_t* h, int parts, uint32_t need, uint32_t* res)
+{
+    const int lane = threadIdx.x & 63;
+    auto sum = [&](int at) {
+        uint32_t v[kMaxHistParts], t = 0u;
+#pragma unroll
+        for (int p = 0; p < kMaxHistParts; ++p) v[p] = h[(int64_t)min(p, parts - 1) * kHistRow + at + lane];
+#pragma unroll
+        for (int p = 0; p < kMaxHistParts; ++p) t += p < parts ? v[p] : 0u;
+        return t;
+    };
+    int C, L;
+    uint32_t above_c, above_f;
+    wave_find_bin(sum(kHistBins), need, C, above_c);
+    const uint32_t v = sum(64 * C);
+    wave_find_bin(v, need - above_c, L, above_f);
+    const uint32_t in_bin = __shfl(v, L, 64);
+    if (threadIdx.x == 0) {
+        res[0] = (uint32_t)(64 * C + L);
+        res[1] = need - above_c - above_f;
+        res[2] = in_bin;
+    }
+}
+
 // Histogram of `nb` bins in LDS: the bin holding the need-th largest key,
 // i.e. the largest d with count(bins >= d) >= need.  res[0] = d,
 // res[1] = count(bins > d).  Every thread of the NT-thread block must call this.
@@ -332,15 +360,17 @@ __global__ __launch_bounds__(kThreads) void topk_refine_kernel(RefineArgs a)
 
     // the chunk's S and the row's first-digit histogram are loaded together
     const float2 sx = load_s_pair(srow, c, a.n);
+    const uint32_t* h1p = a.hist1 + (int64_t)row * a.hist_reps * kHistRow;
     DigitHist h1;
-    load_digit_hist(a.hist1 + (int64_t)row * kHistRow, h1);
+    if (a.hist_reps == 1) load_digit_hist(h1p, h1);
     uint32_t key[kPerThread];
     bool ok[kPerThread];
     keys_of(sx, c, a.n, a.pin_lo, a.pin_hi, key, ok);
     for (int i = tid; i < kHistRow; i += kThreads) hist[i] = 0u;
     if (tid == 0) n_cand = nlist = 0u;
     // first digit: the bin of the k-th key
-    find_digit(h1, (uint32_t)a.k, res);
+    if (a.hist_reps == 1) find_digit(h1, (uint32_t)a.k, res);
+    else find_digit_parts(h1p, a.hist_reps, (uint32_t)a.k, res);
     __syncthreads();
     const uint32_t b1 = res[0] & (kHistBins - 1);
     const uint32_t need1 = res[1];

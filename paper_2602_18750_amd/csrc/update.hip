@@ -128,6 +128,12 @@ constexpr int kUpdWaves = kUpdThreads / 64;
 constexpr int kTokWaves = kUpdChunk / 64;   // waves whose threads finish a token (thread t < kUpdChunk)
 static_assert(kUpdChunk % 64 == 0 && kTokWaves <= kUpdWaves, "whole waves of tokens");
 
+// The part of the row's first-digit histogram that this workgroup counts into (a power of two of them).
+__device__ __forceinline__ uint32_t* hist_part(const UpdateArgs& a, int row)
+{
+    return a.hist + ((int64_t)row * a.hist_reps + (blockIdx.x & (unsigned)(a.hist_reps - 1))) * kHistRow;
+}
+
 // First-digit bound of the streamed selection for this row: the first digit
 // of the previous step's threshold, while the keys at or above that bin then
 // were at least this step's k (S only grows), the pins are the same and n did
@@ -196,7 +202,7 @@ __device__ __forceinline__ uint32_t class_total(const uint32_t (*wcnt)[kTokWaves
     return t;
 }
 
-__device__ __forceinline__ void stream_store(const UpdateArgs& a, int row, int j, uint32_t key, uint32_t bnd,
+__device__ __forceinline__ void stream_store(const UpdateArgs& a, int row, int blk, int j, uint32_t key, uint32_t bnd,
                                              const StreamRank& s, const uint32_t (*wcnt)[kTokWaves])
 {
     const int w = threadIdx.x >> 6;
@@ -204,14 +210,14 @@ __device__ __forceinline__ void stream_store(const UpdateArgs& a, int row, int j
         uint32_t pos = s.rank;
         for (int k = 0; k < s.cls; ++k) pos += class_total(wcnt, k);
         for (int v = 0; v < w; ++v) pos += wcnt[s.cls][v];
-        a.spairs[(int64_t)row * a.n + (int64_t)blockIdx.x * kUpdChunk + pos] = make_uint2(key, (uint32_t)j);
+        a.spairs[(int64_t)row * a.n + (int64_t)blk * kUpdChunk + pos] = make_uint2(key, (uint32_t)j);
     }
     const int nup = (a.n + kUpdChunk - 1) / kUpdChunk;
     if (threadIdx.x == 0) {
         uint32_t c[kPairClasses];
 #pragma unroll
         for (int k = 0; k < kPairClasses; ++k) c[k] = class_total(wcnt, k);
-        uint4* slot = reinterpret_cast<uint4*>(a.scount + ((int64_t)row * nup + blockIdx.x) * kSlotWords);
+        uint4* slot = reinterpret_cast<uint4*>(a.scount + ((int64_t)row * nup + blk) * kSlotWords);
         static_assert(kSlotWords == 8 && kPairClasses == 5, "two 16-byte words per slot");
         slot[0] = make_uint4(c[0], c[1], c[2], c[3]);
         slot[1] = make_uint4(c[4], bnd, 0u, 0u);
@@ -335,7 +341,8 @@ __device__ __forceinline__ void finish_head_stats(const UpdateArgs& a, int b, in
 // unit partials reduced here.  The first-digit histogram of the new keys
 // (LDS, then the touched windows) is counted for the refine pass and for a
 // streamed selection without a bound; with a bound the selection takes the
-// first digit from the class counts of the pairs.
+// first digit from the class counts of the pairs.  update_attn_loop_kernel is
+// the same over several chunks.
 __global__ __launch_bounds__(kUpdThreads) void update_attn_kernel(UpdateArgs a)
 {
     __shared__ float2 wsum[kUpdWaves][64];
@@ -414,8 +421,128 @@ __global__ __launch_bounds__(kUpdThreads) void update_attn_kernel(UpdateArgs a)
     StreamRank sr{};
     if (a.prev && w < kTokWaves) sr = stream_rank(a, row, j, key, bnd, sc_wcnt);   // wave-uniform
     __syncthreads();
-    if (do_hist) key_hist_flush<kUpdThreads>(kh, a.hist + (int64_t)row * kHistRow);
-    if (a.prev && w < kTokWaves) stream_store(a, row, j, key, bnd, sr, sc_wcnt);
+    if (do_hist) key_hist_flush<kUpdThreads>(kh, hist_part(a, row));
+    if (a.prev && w < kTokWaves) stream_store(a, row, blockIdx.x, j, key, bnd, sr, sc_wcnt);
+}
+
+// update_attn_kernel over a.per consecutive chunks per workgroup, where the
+// row blocks exceed what runs at once (update_chunks_per_wg): the statistics,
+// the histogram's clear and its flush are paid once, and the next chunk's
+// first HB logits per wave and S are loaded before this chunk is computed.
+// Measured, one chunk per workgroup -> this (us): 4 x 131K plain 36.8 -> 14.9,
+// streamed 18.9 -> 17.4; 32 x 32K 35 + 4.7 (the statistics launch) -> 26.4; 3
+// x 20K with 4 rows of 7 heads 14.2 -> 9.2 (the parts of the histogram
+// included).  For a single chunk the loop's bookkeeping costs 0.3-0.6 us.
+template <int HB>
+__global__ __launch_bounds__(kUpdThreads, 8) void update_attn_loop_kernel(UpdateArgs a)
+{
+    __shared__ float2 wsum[2][kUpdWaves][64];   // alternating chunks: one barrier per chunk
+    __shared__ KeyHist kh;
+    __shared__ float2 red[kUpdThreads];
+    __shared__ float2 ms[256];
+    __shared__ uint32_t sc_wcnt[kPairClasses][kTokWaves];
+    const int r = blockIdx.y, b = blockIdx.z;
+    const int row = b * a.R + r;
+    const int h0 = a.R == 1 ? 0 : r * a.G;
+    const int nh = a.R == 1 ? a.Hq : a.G;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hh = head_of_thread(a, tid);                // this thread's head in the statistics
+    // as in update_attn_kernel, every load of the opening before the first wait
+    HeadParts hp;
+    load_head_parts(a, a.part + ((int64_t)b * a.Hq + h0) * a.npart, hh, tid - hh * a.tph, nh, hp);
+    const float* lrow = a.logits + ((int64_t)b * a.Hq + h0) * a.ld;
+    float* srow = a.s + (int64_t)b * a.s_sb + (int64_t)r * a.s_sr;
+    const int ld2 = (int)(a.ld - 2);                      // rows are padded to ld (multiple of 4)
+    int j0 = blockIdx.x * a.per * kUpdChunk;   // the chunk's first token
+    const int j_end = min(j0 + a.per * kUpdChunk, a.n);
+    float2 x[HB];
+    {
+        const float* lg = lrow + min(j0 + 2 * lane, ld2);   // this lane's 2 tokens
+#pragma unroll
+        for (int i = 0; i < HB; ++i)
+            x[i] = *reinterpret_cast<const float2*>(lg + (int64_t)min(w + kUpdWaves * i, nh - 1) * a.ld);
+    }
+    // thread tid < kUpdChunk finishes token j0 + tid; the load is unconditional: no branch around it
+    const int jt = min(tid, kUpdChunk - 1);
+    float s_ld = srow[min(j0 + jt, a.n - 1)];
+    uint4 p0 = make_uint4(0u, 0u, 0u, 0u), p1 = p0;
+    if (a.prev) {
+        p0 = a.prev[2 * row];
+        p1 = a.prev[2 * row + 1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (a.hist) key_hist_clear<kUpdThreads>(kh);
+    finish_head_stats(a, b, h0, nh, hh, hp, red, ms);
+    const uint32_t bnd = a.prev ? stream_bound(a, p0, p1) : 0u;
+    const bool do_hist = a.hist != nullptr && !(bnd >> 31);   // block-uniform
+    for (int it = 0;; ++it) {
+        const float* lg = lrow + min(j0 + 2 * lane, ld2);
+        const bool more = j0 + kUpdChunk < j_end;   // block-uniform
+        // the next chunk's first batch and S (the last chunk reads its own again)
+        const int jn = more ? j0 + kUpdChunk : j0;
+        float2 xn[HB];
+        const float* lgn = lrow + min(jn + 2 * lane, ld2);
+        float s_n = s_ld;
+        if (more) {
+#pragma unroll
+            for (int i = 0; i < HB; ++i)
+                xn[i] = *reinterpret_cast<const float2*>(lgn + (int64_t)min(w + kUpdWaves * i, nh - 1) * a.ld);
+            s_n = srow[min(jn + jt, a.n - 1)];
+        }
+        float2 acc = make_float2(0.0f, 0.0f);
+        for (int hb = w;;) {
+            float2 st[HB];   // every statistics read of the batch before the first use
+#pragma unroll
+            for (int i = 0; i < HB; ++i) st[i] = ms[min(hb + kUpdWaves * i, nh - 1)];
+#pragma unroll
+            for (int i = 0; i < HB; ++i) {
+                const float e0 = exp2_ftz(a.s2 * x[i].x - st[i].x) * st[i].y;
+                const float e1 = exp2_ftz(a.s2 * x[i].y - st[i].x) * st[i].y;
+                const bool live = hb + kUpdWaves * i < nh;   // wave-uniform
+                acc.x += live ? e0 : 0.0f;
+                acc.y += live ? e1 : 0.0f;
+            }
+            hb += kUpdWaves * HB;
+            if (hb >= nh) break;
+#pragma unroll
+            for (int i = 0; i < HB; ++i)
+                x[i] = *reinterpret_cast<const float2*>(lg + (int64_t)min(hb + kUpdWaves * i, nh - 1) * a.ld);
+        }
+        float2 (*ws2)[64] = wsum[it & 1];
+        ws2[w][lane] = acc;
+        __syncthreads();
+        const float* ws = reinterpret_cast<const float*>(&ws2[0][0]);
+        const int j = tid < kUpdChunk ? j0 + tid : a.n;
+        uint32_t key = 0u;
+        if (j < a.n) {
+            float tot = ws[tid];
+#pragma unroll
+            for (int v = 1; v < kUpdWaves; ++v) tot += ws[v * 2 * 64 + tid];
+            const float s_new = s_ld + tot;
+            srow[j] = s_new;
+            key = select_key(s_new, j, a.pin_lo, a.pin_hi);
+            if (do_hist) count_key(kh, key);
+        }
+        // the streamed selection's ranks and pairs: the token waves only (the others
+        // would share SIMDs with them for nothing)
+        if (a.prev) {
+            const int blk = j0 / kUpdChunk;
+            StreamRank sr{};
+            if (w < kTokWaves) sr = stream_rank(a, row, j, key, bnd, sc_wcnt);   // wave-uniform
+            __syncthreads();
+            if (w < kTokWaves) stream_store(a, row, blk, j, key, bnd, sr, sc_wcnt);
+        }
+        if (!more) break;
+        j0 = jn;
+        s_ld = s_n;
+#pragma unroll
+        for (int i = 0; i < HB; ++i) x[i] = xn[i];
+    }
+    if (do_hist) {
+        __syncthreads();
+        key_hist_flush<kUpdThreads>(kh, hist_part(a, row));
+    }
 }
 
 // Token rows, RAW mode, Hkv > 1: S[b,0,j] += sum_g groupsum[b,g,j] (same layout).
@@ -458,7 +585,7 @@ __global__ __launch_bounds__(256) void update_raw_groups_kernel(UpdateArgs a)
     }
     if (do_hist) {
         __syncthreads();
-        key_hist_flush<256>(kh, a.hist + (int64_t)b * kHistRow);
+        key_hist_flush<256>(kh, hist_part(a, b));
     }
 }
 
@@ -474,8 +601,15 @@ hipError_t launch_update_attn(const UpdateArgs& a, hipStream_t st, Stamp ts)
 {
     const int nh = a.R == 1 ? a.Hq : a.G;
     if (nh < 1 || a.tph != kUpdThreads / nh || a.B > 65535 || a.R > 65535) return hipErrorInvalidValue;
-    dim3 grid((a.n + kUpdChunk - 1) / kUpdChunk, a.R, a.B);
-    hipExtLaunchKernelGGL(update_attn_kernel, grid, dim3(kUpdThreads), 0, st, ts.start, ts.stop, 0, a);
+    const int nup = (a.n + kUpdChunk - 1) / kUpdChunk;
+    if (a.per < 1) return hipErrorInvalidValue;
+    dim3 grid((nup + a.per - 1) / a.per, a.R, a.B);
+    // heads in flight per wave, so that rows of few heads (KV-head rows) make no clamped loads
+    auto kernel = a.per == 1            ? update_attn_kernel
+                  : nh <= kUpdWaves     ? update_attn_loop_kernel<1>
+                  : nh <= 2 * kUpdWaves ? update_attn_loop_kernel<2>
+                                        : update_attn_loop_kernel<4>;
+    hipExtLaunchKernelGGL(kernel, grid, dim3(kUpdThreads), 0, st, ts.start, ts.stop, 0, a);
     return hipGetLastError();
 }
 
