@@ -51,8 +51,7 @@ __global__ __launch_bounds__(kHeadDim) void attn_combine_kernel(AttnArgs a)
 template <int DT>
 hipError_t launch_attn_dt(const AttnArgs& a, dim3 grid, hipStream_t st)
 {
-    const int gc = (a.G % 8 == 0) ? 8 : (a.G % 4 == 0) ? 4 : (a.G % 2 == 0) ? 2 : 1;
-    switch (gc) {
+    switch (heads_per_pass(a.G)) {
     case 8: hipLaunchKernelGGL((attn_split_kernel<DT, 8>), grid, dim3(256), 0, st, a); break;
     case 4: hipLaunchKernelGGL((attn_split_kernel<DT, 4>), grid, dim3(256), 0, st, a); break;
     case 2: hipLaunchKernelGGL((attn_split_kernel<DT, 2>), grid, dim3(256), 0, st, a); break;

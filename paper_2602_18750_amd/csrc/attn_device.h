@@ -45,6 +45,13 @@ struct AttnLds {
     float o[4][GC][kHeadDim];         // per-wave outputs, added at the end
 };
 
+// Heads of a group handled per pass over its selected rows (1, 2, 4 or 8):
+// the fewest passes, the last one with its heads past G masked (they repeat
+// head G-1 and are not stored).  The rows are read once per pass: the emit
+// kernel of a 3 x 20K step with 7 heads per KV head takes 11.2 us in one masked
+// pass, 22.0 head by head; 2 x 32K with 5 heads 12.1 and 20.6.
+inline int heads_per_pass(int G) { return G > 4 ? 8 : G > 2 ? 4 : G; }
+
 // This lane's 8 query elements of heads g*G+hc .. +GC (16-lane row layout).
 template <int GC>
 __device__ __forceinline__ void load_queries(const AttnArgs& a, int b, int g, int hc, uint4 (&qv)[GC])
@@ -52,7 +59,7 @@ __device__ __forceinline__ void load_queries(const AttnArgs& a, int b, int g, in
     const int l16 = threadIdx.x & 15;
 #pragma unroll
     for (int hh = 0; hh < GC; ++hh) {
-        const int h = g * a.G + hc + hh;
+        const int h = g * a.G + min(hc + hh, a.G - 1);
         qv[hh] = *reinterpret_cast<const uint4*>(a.q + (int64_t)b * a.q_sb + (int64_t)h * a.q_sh + l16 * 8);
     }
 }
@@ -261,7 +268,7 @@ __device__ __forceinline__ void softmax_block(int cnt, AttnLds<GC>& sh)
 
 // weight * V over this wave's entries w, w+4, ... of the block: the first 16
 // (and, when `two`, 32) from the rows already loaded, the rest loaded here.
-template <int DT, int GC, bool TIER = false>
+template <int DT, int GC, bool TIER, bool TWO>
 __device__ __forceinline__ void values_block(const RowSrc& vs, int w, int cnt, int nmine, bool two,
                                              const uint32_t (&vr)[kVBatch], const uint32_t (&vr2)[kVBatch],
                                              AttnAcc<GC>& acc, AttnLds<GC>& sh)
@@ -273,8 +280,9 @@ __device__ __forceinline__ void values_block(const RowSrc& vs, int w, int cnt, i
         acc.o[hh][1] *= al;
     }
     values_rows<DT, GC>(vr, w, 0, nmine, cnt, sh.p, acc);
-    if (two) values_rows<DT, GC>(vr2, w, kVBatch, nmine, cnt, sh.p, acc);
-    for (int i0 = 2 * kVBatch; i0 < nmine; i0 += kVBatch) {   // lists longer than 128
+    if constexpr (TWO)
+        if (two) values_rows<DT, GC>(vr2, w, kVBatch, nmine, cnt, sh.p, acc);
+    for (int i0 = (TWO ? 2 : 1) * kVBatch; i0 < nmine; i0 += kVBatch) {   // longer lists
         uint32_t vx[kVBatch];
         load_v_rows<TIER>(vs, sh.tok, w + 4 * i0, cnt, vx);
         values_rows<DT, GC>(vx, w, i0, nmine, cnt, sh.p, acc);
@@ -286,8 +294,10 @@ __device__ __forceinline__ void values_block(const RowSrc& vs, int w, int cnt, i
 // thread of the workgroup must call this.  The K rows are issued before the
 // V rows, so that the logits wait for K only; every loop bound is
 // wave-uniform.  TIER: a tiered cache, the entries' hot-pool slots in sloc
-// (written with sh.tok).
-template <int DT, int GC, bool TIER = false>
+// (written with sh.tok).  TWO: lists of 65 to 128 entries in one round trip
+// too, at the cost of 32 registers, i.e. of resident workgroups (two_batches
+// in topk.hip).
+template <int DT, int GC, bool TIER = false, bool TWO = true>
 __device__ __forceinline__ void attn_block(const AttnArgs& a, int b, int g, const uint4 (&qv)[GC], int cnt,
                                            AttnAcc<GC>& acc, AttnLds<GC>& sh, const int32_t* sloc = nullptr)
 {
@@ -297,11 +307,11 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int b, int g, cons
     const RowSrc ks = k_src(a, b, g, sloc);
     const RowSrc vs = v_src(a, b, g, sloc);
 
-    // A: logits of every entry, into sh.p.  Up to 128 entries take one round
-    // trip: the K rows of entries < 64 (and < 128 when the list is longer),
-    // then the V rows of this wave's first 16 (and 32) entries.
+    // A: logits of every entry, into sh.p.  Up to 128 (TWO; else 64) entries
+    // take one round trip: the K rows of entries < 64 (and < 128 when the list
+    // is longer), then the V rows of this wave's first 16 (and 32) entries.
     const int nmine = cnt > w ? (cnt - w + 3) / 4 : 0;   // this wave's entries w, w+4, ...
-    const bool two = cnt > 16 * kKBatch;                 // block-uniform
+    const bool two = TWO && cnt > 16 * kKBatch;          // block-uniform
     uint4 kr[kKBatch], kr2[kKBatch];
     load_k_rows<TIER>(ks, sh.tok, rg, cnt, kr);
     if (two) load_k_rows<TIER>(ks, sh.tok, rg + 16 * kKBatch, cnt, kr2);
@@ -311,7 +321,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int b, int g, cons
     if (two) load_v_rows<TIER>(vs, sh.tok, w + 4 * kVBatch, cnt, vr2);
     logits_rows<DT, GC>(a, qv, kr, rg, cnt, (cnt - 4 * w + 15) / 16, sh.p);
     if (two) logits_rows<DT, GC>(a, qv, kr2, rg + 16 * kKBatch, cnt, (cnt - 16 * kKBatch - 4 * w + 15) / 16, sh.p);
-    for (int base = 32 * kKBatch; base < cnt; base += 16 * kKBatch) {   // lists longer than 128
+    for (int base = (TWO ? 32 : 16) * kKBatch; base < cnt; base += 16 * kKBatch) {   // longer lists
         uint4 kx[kKBatch];
         load_k_rows<TIER>(ks, sh.tok, base + rg, cnt, kx);
         logits_rows<DT, GC>(a, qv, kx, base + rg, cnt, (cnt - base - 4 * w + 15) / 16, sh.p);
@@ -319,7 +329,7 @@ __device__ __forceinline__ void attn_block(const AttnArgs& a, int b, int g, cons
     __syncthreads();
 
     softmax_block<GC>(cnt, sh);
-    values_block<DT, GC, TIER>(vs, w, cnt, nmine, two, vr, vr2, acc, sh);
+    values_block<DT, GC, TIER, TWO>(vs, w, cnt, nmine, two, vr, vr2, acc, sh);
 }
 
 // attn_block with the logits already in sh.p (scaled by s2, written with
@@ -337,7 +347,7 @@ __device__ __forceinline__ void attn_block_logits(const AttnArgs& a, int b, int 
     load_v_rows(vs, sh.tok, w, cnt, vr);
     if (two) load_v_rows(vs, sh.tok, w + 4 * kVBatch, cnt, vr2);
     softmax_block<GC>(cnt, sh);
-    values_block<DT, GC>(vs, w, cnt, nmine, two, vr, vr2, acc, sh);
+    values_block<DT, GC, false, true>(vs, w, cnt, nmine, two, vr, vr2, acc, sh);
 }
 
 // Adds the four waves' outputs and writes the partial (m, l, o[D]) of heads
@@ -356,8 +366,9 @@ __device__ __forceinline__ void attn_finish(const AttnArgs& a, int b, int g, int
         const int hh = e / kHeadDim, d = e % kHeadDim;
         const float o = ((sh.o[0][hh][d] + sh.o[1][hh][d]) + sh.o[2][hh][d]) + sh.o[3][hh][d];
         const int64_t pi = ((int64_t)b * a.Hq + g * a.G + hc + hh) * nslots + slot;
-        a.part_o[pi * kHeadDim + d] = o;
-        if (d == 0) a.part_ml[pi] = make_float2(sh.mrun[hh], sh.lrun[hh]);
+        const bool live = hc + hh < a.G;   // not a masked head
+        if (live) a.part_o[pi * kHeadDim + d] = o;
+        if (live && d == 0) a.part_ml[pi] = make_float2(sh.mrun[hh], sh.lrun[hh]);
     }
     __syncthreads();
 }

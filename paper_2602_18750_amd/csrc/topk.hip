@@ -517,16 +517,19 @@ __device__ __forceinline__ void for_row_pairs(const RefineArgs& r, int row, bool
     }
 }
 
-// The scan's logits of heads h0 .. h0+GC of this thread's two tokens of
+// The scan's logits of the first GC heads of group g (heads past G: head G-1) of this thread's two tokens of
 // chunk c (rows of ld floats, ld a multiple of 4; tokens past the row's end
 // read the padded tail or an earlier pair and are never selected).
 template <int GC>
-__device__ __forceinline__ void load_chunk_logits(const AttnArgs& at, int b, int h0, int c, float2 (&lg)[GC])
+__device__ __forceinline__ void load_chunk_logits(const AttnArgs& at, int b, int g, int c, float2 (&lg)[GC])
 {
     const int j = min(c * kSelChunk + (int)threadIdx.x * kPerThread, (int)at.ld - 2);
-    const float* p = at.logits + ((int64_t)b * at.Hq + h0) * at.ld + j;
+    const float* p = at.logits + ((int64_t)b * at.Hq + g * at.G) * at.ld + j;
 #pragma unroll
-    for (int hh = 0; hh < GC; ++hh) lg[hh] = *reinterpret_cast<const float2*>(p + hh * at.ld);
+    for (int hh = 0; hh < GC; ++hh) {
+        lg[hh] = *reinterpret_cast<const float2*>(p);
+        p += hh + 1 < at.G ? at.ld : 0;
+    }
 }
 
 // With LG the attention takes its logits from the scan (at.logits) instead
@@ -534,7 +537,7 @@ __device__ __forceinline__ void load_chunk_logits(const AttnArgs& at, int b, int
 // selected token's K and V rows are read from the hot pool's slot that
 // at.loc gives it, or from the cold pool (its row by position) when that is
 // -1; the slots of the chunk's tokens are loaded with its S.
-template <int DT, int GC, bool ATTN, bool STREAM = false, bool LG = false, bool TIER = false>
+template <int DT, int GC, bool ATTN, bool STREAM = false, bool LG = false, bool TIER = false, bool TWO = true>
 __global__ __launch_bounds__(kThreads) void topk_emit_kernel(RefineArgs r, AttnArgs at)
 {
     static_assert(!TIER || (ATTN && !LG), "a tiered cache gathers K and V for the attention");
@@ -576,7 +579,7 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(RefineArgs r, AttnA
         lv = *reinterpret_cast<const int2*>(at.loc + (int64_t)row * at.loc_sr + (j < r.n ? j : ((r.n - 1) & ~1)));
     }
     float2 lgv[LG ? GC : 1];
-    if constexpr (LG) load_chunk_logits<GC>(at, b, g * at.G, c, lgv);
+    if constexpr (LG) load_chunk_logits<GC>(at, b, g, c, lgv);
     // exact threshold: (key >> shift) compared with prefix; `need` keys equal to it are taken
     uint32_t prefix, need;
     int shift;
@@ -859,11 +862,12 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(RefineArgs r, AttnA
         // the first head chunk with the queries (or logits) loaded at the start
         if (tot) {
             if constexpr (LG) attn_block_logits<DT, GC>(at, b, g, (int)tot, acc, sh);
-            else attn_block<DT, GC, TIER>(at, b, g, qv, (int)tot, acc, sh, sloc);
+            else attn_block<DT, GC, TIER, TWO>(at, b, g, qv, (int)tot, acc, sh, sloc);
         }
         attn_finish<GC>(at, b, g, 0, acc, c, r.nchunks, sh);
-        for (int i = 1; i < ng * (at.G / GC); ++i) {   // further head chunks and KV heads
-            const int gg = g + i / (at.G / GC), hc = (i % (at.G / GC)) * GC;
+        const int np = (at.G + GC - 1) / GC;          // passes per KV head (heads_per_pass)
+        for (int i = 1; i < ng * np; ++i) {           // further head chunks and KV heads
+            const int gg = g + i / np, hc = (i % np) * GC;
             AttnAcc<GC> acc2;
             attn_begin<GC>(acc2, sh);
             if constexpr (LG) {   // the list's logits of these heads
@@ -871,13 +875,13 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(RefineArgs r, AttnA
                 for (uint32_t t = tid; t < tot; t += kThreads) {
                     const int j = sh.tok[t];
 #pragma unroll
-                    for (int hh = 0; hh < GC; ++hh) sh.p[t][hh] = at.s2 * lp[hh * at.ld + j];
+                    for (int hh = 0; hh < GC; ++hh) sh.p[t][hh] = at.s2 * lp[min(hh, at.G - 1 - hc) * at.ld + j];
                 }
                 __syncthreads();
                 if (tot) attn_block_logits<DT, GC>(at, b, gg, (int)tot, acc2, sh);
             } else {
                 load_queries<GC>(at, b, gg, hc, qv);
-                if (tot) attn_block<DT, GC, TIER>(at, b, gg, qv, (int)tot, acc2, sh, sloc);
+                if (tot) attn_block<DT, GC, TIER, TWO>(at, b, gg, qv, (int)tot, acc2, sh, sloc);
             }
             attn_finish<GC>(at, b, gg, hc, acc2, c, r.nchunks, sh);
         }
@@ -959,19 +963,33 @@ __global__ __launch_bounds__(kThreads) void merge_write_kernel(RefineArgs r, Att
     }
 }
 
+// Whether attention that gathers K and V keeps a second batch of rows in
+// registers, so that lists of 65 to 128 entries take one round trip
+// (attn_block's TWO).  Without it four or five workgroups are resident per CU
+// instead of three, which pays once there are more than three and the average
+// list fits one batch (emit, us, with -> without): int4 2 x 100K at 5 % 25.5
+// -> 20.4, int8 8 x 16K at 10 % 20.1 -> 17.1, RAW 8 x 8K 12.7 -> 11.8; 512
+// workgroups (1 x 32K) 10.7 -> 11.2.
+inline bool two_batches(const RefineArgs& r, int64_t wgs)
+{
+    return wgs <= 3 * 256 || (int64_t)r.k * kSelChunk > 56ll * r.n;
+}
+
 template <int DT, int GC, bool STREAM, bool LG, bool TIER>
 void emit_attn_launch(const RefineArgs& r, const AttnArgs& at, hipStream_t st, Stamp ts)
 {
     dim3 grid(r.nchunks, at.B * (at.Hkv / at.kv_per_wg));
-    hipExtLaunchKernelGGL((topk_emit_kernel<DT, GC, true, STREAM, LG, TIER>), grid, dim3(kThreads), 0, st, ts.start,
-                          ts.stop, 0, r, at);
+    auto kernel = topk_emit_kernel<DT, GC, true, STREAM, LG, TIER>;
+    if constexpr (!LG && !TIER) {
+        if (!two_batches(r, (int64_t)grid.x * grid.y)) kernel = topk_emit_kernel<DT, GC, true, STREAM, LG, TIER, false>;
+    }
+    hipExtLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, ts.start, ts.stop, 0, r, at);
 }
 
 template <int DT, bool STREAM, bool LG, bool TIER = false>
 void emit_attn_gc(const RefineArgs& r, const AttnArgs& at, hipStream_t st, Stamp ts)
 {
-    const int gc = (at.G % 8 == 0) ? 8 : (at.G % 4 == 0) ? 4 : (at.G % 2 == 0) ? 2 : 1;
-    switch (gc) {
+    switch (heads_per_pass(at.G)) {
     case 8: emit_attn_launch<DT, 8, STREAM, LG, TIER>(r, at, st, ts); break;
     case 4: emit_attn_launch<DT, 4, STREAM, LG, TIER>(r, at, st, ts); break;
     case 2: emit_attn_launch<DT, 2, STREAM, LG, TIER>(r, at, st, ts); break;
