@@ -414,6 +414,10 @@ hill_status run_select(const hill_desc* d, const Shape& s, const Layout& L, cons
                        int32_t* idx, float* val, void* ws, hipStream_t st)
 {
     const RefineArgs r = refine_args(d, s, L, sacc, ksel, ws);
+    if (s.n <= kRowTopkTokens) {
+        HIP_TRY(launch_row_topk(r, s.B * s.R, idx, val, st));
+        return HILL_OK;
+    }
     HIP_TRY(launch_fill_zero(at<uint32_t>(ws, L.zero), L.zero_words, st));
     HIP_TRY(launch_topk_hist(sacc, d->s_stride_b, d->s_stride_r, s.B, s.R, s.n, s.pin_lo, s.pin_hi,
                              at<uint32_t>(ws, L.hist1), st));
@@ -549,8 +553,13 @@ hill_status run_step(const hill_desc* d, const void* q, const void* k, const voi
     const hill_step_events none{};
     const hill_step_events& e = ev ? *ev : none;
     uint4* state4 = reinterpret_cast<uint4*>(stream_state);
+    // short rows: one launch counts its own digits, selects, attends and writes the outputs (a streamed
+    // step's bound too, so that the sequence goes on from it on longer rows)
+    const bool kgather = s.mode != HILL_SCORE_ATTN || sk.k8;   // as a.logits below
+    const bool short_row = row_step(s.B, s.Hkv, s.n, k_sel, kgather);
     // a reset step selects through the refine pass and only writes the bound
-    HILL_TRY(run_score(d, s, L, q, k, sk, s_acc, ws, true, st, e, stream_reset ? nullptr : state4, k_sel));
+    HILL_TRY(run_score(d, s, L, q, k, sk, s_acc, ws, !short_row, st, e, stream_reset || short_row ? nullptr : state4,
+                       k_sel));
     RefineArgs r = refine_args(d, s, L, s_acc, k_sel, ws);
     AttnArgs a = attn_args(d, s, L, q, k, v, idx_out, k_sel, out, ws);
     if (s.mode == HILL_SCORE_ATTN && !sk.k8) {   // the scan's logits are those of the 16-bit keys: reused
@@ -566,6 +575,11 @@ hill_status run_step(const hill_desc* d, const void* q, const void* k, const voi
         a.hk_sh = a.hv_sh = tier.t->hot_stride_h;
         a.hk_sn = a.hv_sn = tier.t->hot_stride_n;
         a.cap = tier.t->capacity;
+    }
+    if (short_row) {
+        r.state_out = state4;
+        HIP_TRY(launch_row_attend(r, a, s.dtype, idx_out, st, stage(e, HILL_STAGE_SELECT)));
+        return HILL_OK;
     }
     if (state4 && !stream_reset) {   // no refine pass
         r.state_out = state4;

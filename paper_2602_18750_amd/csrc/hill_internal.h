@@ -327,6 +327,26 @@ hipError_t launch_topk_emit_lists(const RefineArgs& r, int rows, hipStream_t st)
 hipError_t launch_topk_emit_attn(const RefineArgs& r, const AttnArgs& at, int dtype, hipStream_t st, Stamp ts = {});
 hipError_t launch_merge_write(const RefineArgs& r, const AttnArgs& at, int32_t* idx, int rows, hipStream_t st,
                               Stamp ts = {});
+// Short rows end their step in one launch (row_attend in row.hip) after the
+// update: at most kRowTokens tokens and kRowPicks selected ones.  One workgroup
+// per KV head then gathers the whole list, so where K rows are gathered too (a
+// sketch's or RAW scores: kgather) a long list wants many KV heads.  Whole
+// steps per layer, refine / emit / merge -> row_attend (us): GQA 32/8, 10 %,
+// 1 x 2K 23.3 -> 19.3, 1 x 4K 24.3 -> 21.2, 32 x 4K at 20 % 90.4 -> 77.7; MHA
+// 1 x 4K at 20 % 26.9 -> 23.0, 8 x 4K 75.5 -> 67.3; int8 8 x 4K 31.7 -> 31.0,
+// 32 x 4K 70 -> 58; int4 1 x 4K (409 picks, 8 KV heads) 24.3 -> 25.4.  At 8K
+// tokens one workgroup's gather takes longer than the launches it saves.
+constexpr int kRowTokens = 4096;
+constexpr int kRowPicks = 1024;
+inline bool row_step(int B, int Hkv, int n, int k, bool kgather)
+{
+    return n <= kRowTokens && k <= kRowPicks && (!kgather || k <= 256 || (int64_t)B * Hkv >= 64);
+}
+// The selection alone (row_topk) holds rows of up to kRowTopkTokens tokens.
+constexpr int kRowTopkTokens = 32768;
+hipError_t launch_row_attend(const RefineArgs& r, const AttnArgs& at, int dtype, int32_t* idx, hipStream_t st,
+                             Stamp ts = {});
+hipError_t launch_row_topk(const RefineArgs& r, int rows, int32_t* idx, float* val, hipStream_t st);
 hipError_t launch_attn_split(const AttnArgs& a, int dtype, hipStream_t st);
 hipError_t launch_attn_combine(const AttnArgs& a, hipStream_t st, Stamp ts = {});
 
