@@ -1,6 +1,12 @@
 // Bidirectional KV Cache Pools (Sec. 4.2, HKM / BKP) on gfx950: the per-token
 // hit-rate table and the hot/cold pool policy, one pass after each decoding
-// step.  Six launches, each parallel over the row's tokens:
+// step.  Rows of up to kRowBkpTokens tokens take one launch:
+//
+//  bkp_row     one workgroup per row, its hits, pool bytes and rank values in
+//              registers and the selected set as a bitmap in LDS
+//
+// Longer rows, and tables that vector loads cannot read, take six, each
+// parallel over the row's tokens:
 //
 //  bkp_hits    one hit for every token of the step's selected set (2-byte
 //              counters, saturating; indices are unique within a row, so each
@@ -14,8 +20,7 @@
 //  bkp_count   per chunk: how many tokens become hot / cold
 //  bkp_write   per chunk: the new pool bytes, and the promotions and
 //              demotions written in token order after the earlier chunks'
-#include "hill_device.h"
-#include "hill_internal.h"
+#include "row_device.h"
 
 namespace hill {
 
@@ -177,7 +182,149 @@ __global__ __launch_bounds__(256) void bkp_write_kernel(BkpArgs a)
     }
 }
 
+// The whole pass of one row (see the six kernels above for each rule): every
+// launch of the long form costs 3 to 5 us for microseconds of work at these
+// sizes (2 x 16K: 28 us and five boundaries, here 16.9).  Groups of eight tokens per lane are read and
+// written as vectors (bkp_row_fits), a last partial group token by token.
+template <int TPT>
+__global__ __launch_bounds__(kRowThreads) void bkp_row_kernel(BkpArgs a)
+{
+    constexpr int kGroups = TPT / 8;
+    __shared__ RowLds rl;
+    __shared__ __attribute__((aligned(16))) uint32_t bins[row_bin_words(8)];
+    __shared__ uint32_t hit[TPT * kRowThreads / 32];   // the step's selected set
+    const int row = blockIdx.x, tid = threadIdx.x;
+    auto token = [](int e) { return row_token<TPT, 8>(e); };
+    for (int i = tid; i < TPT * kRowThreads / 32; i += kRowThreads) hit[i] = 0u;
+    uint16_t* hits = a.hits + a.off(row);
+    uint8_t* hot = a.hot + a.off(row);
+    uint32_t hv[TPT / 2];    // hit counts, two per word
+    uint32_t was = 0u;       // pool bits before the call
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        const int j = token(8 * g);
+        uint32_t* h2 = hv + 4 * g;
+        uint32_t o4[2] = {0u, 0u};           // four pool bytes per word
+        if (j + 8 <= a.n) {
+            const uint4 h = *reinterpret_cast<const uint4*>(hits + j);
+            const uint2 o = *reinterpret_cast<const uint2*>(hot + j);
+            h2[0] = h.x;
+            h2[1] = h.y;
+            h2[2] = h.z;
+            h2[3] = h.w;
+            o4[0] = o.x;
+            o4[1] = o.y;
+        } else {
+            h2[0] = h2[1] = h2[2] = h2[3] = 0u;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (j + e < a.n) {
+                    h2[e >> 1] |= (uint32_t)hits[j + e] << (16 * (e & 1));
+                    o4[e >> 2] |= (uint32_t)hot[j + e] << (8 * (e & 3));
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) was |= ((o4[e >> 2] >> (8 * (e & 3))) & 1u) << (8 * g + e);
+    }
+    __syncthreads();
+    for (int i = tid; i < a.k; i += kRowThreads) {
+        const int j = a.idx[(int64_t)row * a.k + i];
+        if ((unsigned)j < (unsigned)a.n) atomicOr(&hit[j >> 5], 1u << (j & 31));
+    }
+    __syncthreads();
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        const int j = token(8 * g);
+        mine |= ((hit[j >> 5] >> (j & 31)) & 0xffu) << (8 * g);
+    }
+    // rank values as in bkp_rank_kernel, as integers (the window's -1 below all of them)
+    uint32_t key[TPT];
+    bool ok[TPT], sel[TPT];
+#pragma unroll
+    for (int e = 0; e < TPT; ++e) {
+        const int j = token(e);
+        uint32_t h = (hv[e >> 1] >> (16 * (e & 1))) & 0xffffu;
+        if ((mine >> e) & 1u && h != 0xffffu) {
+            ++h;
+            hv[e >> 1] += 1u << (16 * (e & 1));
+        }
+        ok[e] = j < a.n;
+        sel[e] = false;
+        const uint32_t pos = kPosBins - 1u - ((uint32_t)j >> a.pos_shift);
+        key[e] = j >= a.n - a.w ? 0u : ((2u * h + ((was >> e) & 1u)) * kPosBins + pos + 1u) << 7;
+    }
+    // the hit counts of the selected tokens (before the selection, which needs the registers)
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        const int j = token(8 * g);
+        const uint32_t m8 = (mine >> (8 * g)) & 0xffu;
+        if (m8 && j + 8 <= a.n) {
+            *reinterpret_cast<uint4*>(hits + j) = make_uint4(hv[4 * g], hv[4 * g + 1], hv[4 * g + 2], hv[4 * g + 3]);
+        } else if (m8) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)   // only tokens below n are marked
+                if ((m8 >> e) & 1u) hits[j + e] = (uint16_t)(hv[4 * g + (e >> 1)] >> (16 * (e & 1)));
+        }
+    }
+    uint32_t at[kGroups];
+    if (a.f > 0) row_select<TPT, 8, 8>(key, ok, (uint32_t)a.f, rl, bins, sel, at);
+    uint32_t now = 0u, moves[kGroups];   // promotions in the low half, demotions in the high half (at most 32768 each)
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) moves[g] = 0u;
+#pragma unroll
+    for (int e = 0; e < TPT; ++e) {
+        const bool hot_now = ok[e] && (sel[e] || token(e) >= a.n - a.w), hot_was = (was >> e) & 1u;
+        now |= (hot_now ? 1u : 0u) << e;
+        moves[e / 8] += (hot_now && !hot_was ? 1u : 0u) + (hot_was && !hot_now ? 0x10000u : 0u);
+    }
+    __syncthreads();   // row_select's last scan has been read
+    row_positions<kGroups>(moves, rl.wave[1], at);
+    if (tid == kRowThreads - 1) {
+        const uint32_t total = at[kGroups - 1] + moves[kGroups - 1];
+        a.counts[2 * (int64_t)row] = (int32_t)(total & 0xffffu);
+        a.counts[2 * (int64_t)row + 1] = (int32_t)(total >> 16);
+    }
+    int32_t* pro = a.promote + (int64_t)row * a.list_cap;
+    int32_t* dem = a.demote + (int64_t)row * a.list_cap;
+#pragma unroll
+    for (int e = 0; e < TPT; ++e) {
+        const uint32_t n1 = (now >> e) & 1u, w1 = (was >> e) & 1u;
+        if (n1 == w1) continue;
+        const uint32_t p = n1 ? at[e / 8] & 0xffffu : at[e / 8] >> 16;
+        if (p < (uint32_t)a.list_cap) (n1 ? pro : dem)[p] = token(e);
+        at[e / 8] += n1 ? 1u : 0x10000u;
+    }
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        const int j = token(8 * g);
+        if (j + 8 <= a.n) {
+            uint32_t o4[2] = {0u, 0u};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o4[e >> 2] |= ((now >> (8 * g + e)) & 1u) << (8 * (e & 3));
+            *reinterpret_cast<uint2*>(hot + j) = make_uint2(o4[0], o4[1]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (j + e < a.n) hot[j + e] = (uint8_t)((now >> (8 * g + e)) & 1u);
+        }
+    }
+}
+
 }  // namespace
+
+bool bkp_row_fits(const BkpArgs& a)
+{
+    return a.n <= kRowBkpTokens && a.sb % 8 == 0 && a.sr % 8 == 0 && ((uintptr_t)a.hits & 15u) == 0 &&
+           ((uintptr_t)a.hot & 7u) == 0;
+}
+
+hipError_t launch_bkp_row(const BkpArgs& a, int rows, hipStream_t st)
+{
+    auto kernel = a.n <= 8 * kRowThreads ? bkp_row_kernel<8> : bkp_row_kernel<16>;
+    hipLaunchKernelGGL(kernel, dim3(rows), dim3(kRowThreads), 0, st, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_bkp_hits(const BkpArgs& a, int rows, hipStream_t st)
 {

@@ -779,6 +779,10 @@ hill_status hill_bkp_update(const hill_bkp_desc* d, const int32_t* idx, int32_t 
     a.demote = demote;
     a.list_cap = list_cap;
     a.counts = counts;
+    if (bkp_row_fits(a)) {
+        HIP_TRY(launch_bkp_row(a, rows, st));
+        return HILL_OK;
+    }
     HIP_TRY(launch_bkp_hits(a, rows, st));
     if (a.f > 0) {   // frequency slots: the exact top-f of the rank values, ties to the lower index
         HIP_TRY(launch_bkp_rank(a, rows, st));

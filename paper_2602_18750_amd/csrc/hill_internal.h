@@ -254,6 +254,12 @@ struct BkpArgs {
     int32_t* counts;          // [rows, 2]
     __host__ __device__ int64_t off(int row) const { return (int64_t)(row / R) * sb + (int64_t)(row % R) * sr; }
 };
+// The whole pass in one launch: rows of at most kRowBkpTokens tokens (more would need 32 per thread, which
+// do not fit the registers) whose tables allow 16-byte (hits) and
+// 8-byte (pool bytes) accesses.
+constexpr int kRowBkpTokens = 16384;
+bool bkp_row_fits(const BkpArgs& a);
+hipError_t launch_bkp_row(const BkpArgs& a, int rows, hipStream_t st);
 hipError_t launch_bkp_hits(const BkpArgs& a, int rows, hipStream_t st);
 hipError_t launch_bkp_rank(const BkpArgs& a, int rows, hipStream_t st);
 hipError_t launch_bkp_lists(const BkpArgs& a, int rows, hipStream_t st);
@@ -342,7 +348,8 @@ inline bool row_step(int B, int Hkv, int n, int k, bool kgather)
 {
     return n <= kRowTokens && k <= kRowPicks && (!kgather || k <= 256 || (int64_t)B * Hkv >= 64);
 }
-// The selection alone (row_topk) holds rows of up to kRowTopkTokens tokens.
+// The selection alone (row_topk) holds rows of up to kRowTopkTokens tokens: 2 x 16K in 13.7 us instead of five
+// launches of 18 and their boundaries.
 constexpr int kRowTopkTokens = 32768;
 hipError_t launch_row_attend(const RefineArgs& r, const AttnArgs& at, int dtype, int32_t* idx, hipStream_t st,
                              Stamp ts = {});

@@ -21,12 +21,14 @@ namespace hill {
 namespace {
 
 constexpr int kRowV = 4;         // output dimensions per lane: 8-byte loads of a V row
+constexpr int kRowCopies = 4;    // of the digit counts: they lie where the weights and outputs go later
 constexpr int kRowBatch = 8;     // V loads in flight per lane and buffer (two buffers)
 
 template <int GC>
 struct RowAttnLds {
     int32_t tok[kRowPicks];
     union {
+        alignas(16) uint32_t bins[row_bin_words(kRowCopies)];   // the selection's
         float p[kRowPicks][GC];                      // logits, then weights
         float o[kRowWaves * 64 * kRowV * GC];        // the lanes' outputs, once every weight has been read
     };
@@ -51,25 +53,27 @@ __global__ __launch_bounds__(kRowThreads) void row_attend_kernel(RefineArgs r, A
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ds = blockIdx.x % DSPLIT, g = blockIdx.x / DSPLIT, b = blockIdx.y;
     const int row = r.R == 1 ? b : b * at.Hkv + g;
-    const int j0 = TPT * tid;
+    constexpr int GS = TPT < 4 ? TPT : 4;
+    static_assert(TPT == GS, "one group per thread");
+    const int j0 = row_token<TPT, GS>(0);
 
     float sx[TPT];
-    row_load<TPT>(r.s + (int64_t)b * r.s_sb + (int64_t)(r.R == 1 ? 0 : g) * r.s_sr, r.n, sx);
+    row_load<TPT, GS>(r.s + (int64_t)b * r.s_sb + (int64_t)(r.R == 1 ? 0 : g) * r.s_sr, r.n, sx);
     // the first pass's logits of this thread's tokens, in flight during the selection
     float lg[LG ? GC : 1][TPT];
     if constexpr (LG) {
         const float* p = at.logits + ((int64_t)b * at.Hq + g * at.G) * at.ld;
 #pragma unroll
         for (int hh = 0; hh < GC; ++hh) {
-            row_load<TPT>(p, r.n, lg[hh]);
+            row_load<TPT, GS>(p, r.n, lg[hh]);
             p += hh + 1 < at.G ? at.ld : 0;   // heads past G repeat the last (masked below)
         }
     }
     uint32_t key[TPT];
     bool ok[TPT], sel[TPT];
-    row_keys<TPT>(sx, r.n, r.pin_lo, r.pin_hi, key, ok);
-    uint32_t before;
-    const RowBound bound = row_select<TPT>(key, ok, (uint32_t)r.k, rl, sel, before);
+    row_keys<TPT, GS>(sx, r.n, r.pin_lo, r.pin_hi, key, ok);
+    uint32_t before[1];
+    const RowBound bound = row_select<TPT, GS, kRowCopies>(key, ok, (uint32_t)r.k, rl, sh.bins, sel, before);
     const bool writer = ds == 0 && (r.R != 1 || g == 0);
     if (r.state_out && writer && tid == 0) {
         r.state_out[2 * row] = make_uint4(bound.b1 << 20, (uint32_t)r.k - bound.need1 + bound.in1, (uint32_t)r.n, 1u);
@@ -77,7 +81,7 @@ __global__ __launch_bounds__(kRowThreads) void row_attend_kernel(RefineArgs r, A
     }
     const int cnt = r.k;
     {
-        uint32_t p = before;
+        uint32_t p = before[0];
 #pragma unroll
         for (int e = 0; e < TPT; ++e)
             if (sel[e] && p < (uint32_t)cnt) {   // exactly k are selected
@@ -247,24 +251,26 @@ template <int TPT>
 __global__ __launch_bounds__(kRowThreads) void row_topk_kernel(RefineArgs r, int32_t* idx, float* val)
 {
     __shared__ RowLds rl;
+    __shared__ __attribute__((aligned(16))) uint32_t bins[row_bin_words(8)];
     const int row = blockIdx.x, b = row / r.R;
     const float* srow = r.s + (int64_t)b * r.s_sb + (int64_t)(row % r.R) * r.s_sr;
+    constexpr int GS = 4;
     uint32_t key[TPT];
     bool ok[TPT], sel[TPT];
     {
         float sx[TPT];
-        row_load<TPT>(srow, r.n, sx);
-        row_keys<TPT>(sx, r.n, r.pin_lo, r.pin_hi, key, ok);
+        row_load<TPT, GS>(srow, r.n, sx);
+        row_keys<TPT, GS>(sx, r.n, r.pin_lo, r.pin_hi, key, ok);
     }
-    uint32_t p;
-    row_select<TPT>(key, ok, (uint32_t)r.k, rl, sel, p);
+    uint32_t p[TPT / GS];
+    row_select<TPT, GS, 8>(key, ok, (uint32_t)r.k, rl, bins, sel, p);
 #pragma unroll
     for (int e = 0; e < TPT; ++e)
-        if (sel[e] && p < (uint32_t)r.k) {
-            const int j = TPT * (int)threadIdx.x + e;
-            idx[(int64_t)row * r.k + p] = j;
-            if (val) val[(int64_t)row * r.k + p] = srow[j];   // read again: the keys fill the registers
-            ++p;
+        if (sel[e] && p[e / GS] < (uint32_t)r.k) {
+            const int j = row_token<TPT, GS>(e);
+            idx[(int64_t)row * r.k + p[e / GS]] = j;
+            if (val) val[(int64_t)row * r.k + p[e / GS]] = srow[j];   // read again: the keys fill the registers
+            ++p[e / GS];
         }
 }
 
@@ -313,7 +319,7 @@ hipError_t launch_row_attend(const RefineArgs& r, const AttnArgs& at, int dtype,
 
 hipError_t launch_row_topk(const RefineArgs& r, int rows, int32_t* idx, float* val, hipStream_t st)
 {
-    auto kernel = r.n <= 8 * kRowThreads ? row_topk_kernel<8> : row_topk_kernel<32>;
+    auto kernel = r.n <= 8 * kRowThreads ? row_topk_kernel<8> : r.n <= 16 * kRowThreads ? row_topk_kernel<16> : row_topk_kernel<32>;
     hipLaunchKernelGGL(kernel, dim3(rows), dim3(kRowThreads), 0, st, r, idx, val);
     return hipGetLastError();
 }
