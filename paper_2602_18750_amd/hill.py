@@ -225,29 +225,29 @@ def make_desc(q: Optional[torch.Tensor], k: Optional[torch.Tensor], v: Optional[
     d.sm_scale = float(sm_scale)
     d.n_sink, d.n_recent = int(n_sink), int(n_recent)
     if q is not None:
-        d.q_stride_b, d.q_stride_h = q.stride(0), q.stride(1)
-        _require_unit_last(q, "q")
+        d.q_stride_b, d.q_stride_h, last = q.stride()
+        _require_unit_last(last, "q")
     else:
         d.q_stride_b, d.q_stride_h = Hq * D, D
     if k is not None:
-        d.k_stride_b, d.k_stride_h, d.k_stride_n = k.stride(0), k.stride(1), k.stride(2)
-        _require_unit_last(k, "k")
+        d.k_stride_b, d.k_stride_h, d.k_stride_n, last = k.stride()
+        _require_unit_last(last, "k")
     else:
         d.k_stride_b, d.k_stride_h, d.k_stride_n = Hkv * n * D, n * D, D
     if v is not None:
-        d.v_stride_b, d.v_stride_h, d.v_stride_n = v.stride(0), v.stride(1), v.stride(2)
-        _require_unit_last(v, "v")
+        d.v_stride_b, d.v_stride_h, d.v_stride_n, last = v.stride()
+        _require_unit_last(last, "v")
     else:
         d.v_stride_b, d.v_stride_h, d.v_stride_n = d.k_stride_b, d.k_stride_h, d.k_stride_n
     if s is not None:
-        d.s_stride_b, d.s_stride_r = s.stride(0), s.stride(1)
-        if s.stride(2) != 1:
+        d.s_stride_b, d.s_stride_r, last = s.stride()
+        if last != 1:
             raise ValueError("s must have a contiguous token axis")
     return d
 
 
-def _require_unit_last(t: torch.Tensor, name: str):
-    if t.stride(-1) != 1:
+def _require_unit_last(stride: int, name: str):
+    if stride != 1:
         raise ValueError("%s must have a contiguous last (head_dim) axis" % name)
 
 
@@ -274,8 +274,8 @@ def workspace(desc: HillDesc, k_sel: int, device) -> torch.Tensor:
 
 
 def _stream_ptr(stream) -> int:
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:   # the current device's current stream, without building a Stream object (2.8 us)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
