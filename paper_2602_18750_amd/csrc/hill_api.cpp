@@ -557,7 +557,9 @@ hill_status run_step(const hill_desc* d, const void* q, const void* k, const voi
     // step's bound too, so that the sequence goes on from it on longer rows)
     const bool kgather = s.mode != HILL_SCORE_ATTN || sk.k8;   // as a.logits below
     const bool short_row = row_step(s.B, s.Hkv, s.n, k_sel, kgather);
-    // a reset step selects through the refine pass and only writes the bound
+    // a reset step, and a streamed one over very many tokens, selects through the refine pass and only
+    // writes the bound
+    if (state4 && (int64_t)s.B * s.R * s.n > kStreamMaxTokens) stream_reset = true;
     HILL_TRY(run_score(d, s, L, q, k, sk, s_acc, ws, !short_row, st, e, stream_reset || short_row ? nullptr : state4,
                        k_sel));
     RefineArgs r = refine_args(d, s, L, s_acc, k_sel, ws);

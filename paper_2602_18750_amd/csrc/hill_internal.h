@@ -96,6 +96,15 @@ struct UpdateArgs {
     int k;                   // this step's budget
 };
 
+// A streamed step over more tokens than this (rows of all sequences together)
+// selects through the refine pass, as a reset step does, and writes the bound
+// from it: its results are the same, and the walks of long pair lists in every
+// workgroup cost more than the refine launch.  Whole steps, streamed -> refine
+// (us): 4 x 64K 152.4 -> 149.4, 32 x 8K 149.8 -> 147.0, 16 x 30K 256.7 ->
+// 247.0, 4 x 131K 277 -> 271; on the other side 1 x 131K 102.1 and 104.4 per
+// layer, 4 x 32K 84.1 and 85.3, 1 x 32K 31.8 and 35.6.
+constexpr int64_t kStreamMaxTokens = 192 << 10;
+
 // Per-row state of the streamed selection, caller-owned between steps, two
 // uint4: (threshold key, keys whose first digit reached the threshold's, n,
 // valid) and (sink tokens, recent tokens, 0, 0).  The threshold's first digit
