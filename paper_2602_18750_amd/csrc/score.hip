@@ -900,6 +900,38 @@ struct UnitKeysF16 : KeysF16Mfma<DT> {
     }
 };
 
+// UnitKeysF16 for score_tiles: both of a wave's tiles requested at once.
+template <int DT>
+struct KeysF16MfmaPair : KeysF16Mfma<DT> {
+    static constexpr int kSlots = 2;
+    uint4 ks[2][8];
+
+    template <int SLOT>
+    __device__ __forceinline__ void load(const ScoreArgs& a, const TileCoord& c, int rg, int l8)
+    {
+        const int lane = rg * 8 + l8;
+        const int i = lane & 15, q = i >> 2, u = (i >> 1) & 1, p = i & 1;
+        const uint32_t sn2 = (uint32_t)(a.k_sn * 2);
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.k + (int64_t)c.b * a.k_sb + (int64_t)c.g * a.k_sh,
+                                                    (uint32_t)(a.n - 1) * sn2 + 2u * kHeadDim);
+        const uint32_t t = (uint32_t)(c.j0 + 8 * q + 4 * u) * sn2 + (uint32_t)(2 * (lane >> 4) + p) * 16u;
+#pragma unroll
+        for (int gr = 0; gr < 4; ++gr)
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                ks[SLOT][2 * gr + s] = __builtin_bit_cast(
+                    uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(t + (uint32_t)gr * sn2 + 128u * s), 0, kAuxNt));
+    }
+
+    template <int SLOT>
+    __device__ __forceinline__ void dots(int lane, float (&out)[4])
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) this->kr[0][i] = ks[SLOT][i];
+        KeysF16Mfma<DT>::template dots<0>(lane, out);
+    }
+};
+
 // The sketch sources: KEYS = KeysSketchMfma8<DT> or KeysSketchMfma4<DT>, whose
 // group's queries are cast into the wave's own LDS.
 template <int DT, typename KEYS, int BITS>
@@ -1095,6 +1127,13 @@ int resident_per_cu(K kernel)
     return v;
 }
 
+// Buffer offsets are 32 bits: key rows up to two units past n must lie below
+// 4 GiB from the first.
+inline bool buffer_reaches(const ScoreArgs& a)
+{
+    return ((int64_t)a.n + 2 * kUnitTokens) * a.k_sn * 2 < (1ll << 32);
+}
+
 // Whether a matrix-core scan of ATTN logits runs as score_units (whole units
 // per wave) instead of score_tiles (a unit per workgroup).  Measured (us,
 // score_tiles -> score_units; GQA 32/8 unless said):
@@ -1109,13 +1148,11 @@ int resident_per_cu(K kernel)
 //     keep in flight, and unpacking codes costs the vector form more): 2 x 32K
 //     14.2 -> 12.7, 4 x 32K 27.6 -> 20.0, 4 x 131K 94 -> 61, MHA 8 x 4K 23.5
 //     -> 20.5; 1 x 32K 9.5 -> 9.9
-// The descriptor's offsets are 32 bits: key rows up to two units past n must
-// lie below 4 GiB from the first.
 inline bool use_units(const ScoreArgs& a, int64_t total, int ncu)
 {
     if (a.G > kMfmaHeads) return false;
     if (a.k8) return a.kbits == 4 ? total >= 8ll * ncu : a.G >= 4 && total >= 16ll * ncu;
-    return a.G >= 4 && total >= 16ll * ncu && ((int64_t)a.n + 2 * kUnitTokens) * a.k_sn * 2 < (1ll << 32);
+    return a.G >= 4 && total >= 16ll * ncu && buffer_reaches(a);
 }
 
 template <typename Keys>
@@ -1156,8 +1193,15 @@ hipError_t launch_score_inst(const ScoreArgs& a, int ncu, hipStream_t st, Stamp 
             hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
             return hipGetLastError();
         }
-        // 16-bit keys, G >= 4: the dots on the matrix cores as well
+        // 16-bit keys, G >= 4: the dots on the matrix cores as well; with at most two units per CU both of
+        // a wave's tiles are requested at once (KeysF16MfmaPair; whole steps, one tile at a time -> both:
+        // 1 x 8K 25.7 -> 25.1 us per layer; 1 x 16K even, 1 x 32K 31.7 -> 32.2, longer ones within 1 %)
         if (!a.k8 && a.G >= 4) {
+            if (total <= 2ll * ncu && buffer_reaches(a)) {
+                hipExtLaunchKernelGGL((score_tiles_kernel<1, OUT, KeysF16MfmaPair<DT>>), dim3((unsigned)(total < 1 ? 1 : total)),
+                                      dim3(256), 0, st, ts.start, ts.stop, 0, a);
+                return hipGetLastError();
+            }
             auto kernel = score_tiles_kernel<1, OUT, KeysF16Mfma<DT>>;
             const int64_t cap = (int64_t)ncu * resident_per_cu(kernel);
             const int64_t grid = total < cap ? (total < 1 ? 1 : total) : cap;
