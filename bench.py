@@ -788,7 +788,7 @@ def make_step_counters(directory: str, command: str):
     w = W.WORKLOADS[COUNTERS_WORKLOAD]
     alg = step_algorithmic_bytes(w.batch, w.n_q_heads, w.n_kv_heads, w.head_dim, w.n_tokens, w.k_sel)
     names = {"update_attn": r"update_attn_kernel",
-             "topk_emit": r"topk_emit_kernel<1, 4, true, true, true, false>",
+             "topk_emit": r"topk_emit_kernel<1, 4, true, true, true, false, true>",
              "merge_write": r"merge_write_kernel"}
     rec = {"workload": w.name, "source_sha256": step_sources_sha(), "fetch_factor": round(ff, 4),
            "write_factor": round(wf, 4), "kernels": {}, "command": command}
@@ -940,7 +940,7 @@ def summarize_sweep(directory: str):
         raise SystemExit("no kernel trace under %s" % directory)
     with open(path[0]) as f:
         rows = sorted(csv.DictReader(f), key=lambda r: int(r["Start_Timestamp"]))
-    kinds = (("scan", "score_tiles_kernel"), ("stats", "softmax_stats_kernel"), ("update", "update_attn_kernel"),
+    kinds = (("scan", "score_"), ("stats", "softmax_stats_kernel"), ("update", "update_attn_"),   # either form
              ("refine", "topk_refine_kernel"), ("select", "topk_emit_kernel"), ("merge", "merge_write_kernel"))
     # one step per scan launch: the kernels up to the next scan belong to it
     # (softmax_stats runs only where the update does not reduce the partials)
