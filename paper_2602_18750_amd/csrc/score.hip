@@ -1115,16 +1115,29 @@ __global__ __launch_bounds__(256, 4) void score_units_kernel(ScoreArgs a)
     }
 }
 
-// Workgroups of `kernel` that stay resident on one CU (queried once per instantiation).
-template <typename K>
-int resident_per_cu(K kernel)
+// Workgroups of Kernel that stay resident on one CU, queried once per kernel.
+// (Keyed by the kernel itself: every scan has the same function type, and one
+// shared answer let the first scan of a process size all later grids; 4 x 131K
+// after a 1 x 32K scan ran 1536 workgroups where 1024 are resident.)
+template <auto Kernel>
+int resident_per_cu()
 {
-    static const int v = [kernel] {
+    static const int v = [] {
         int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 256, 0) != hipSuccess || nb < 1) nb = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, Kernel, 256, 0) != hipSuccess || nb < 1) nb = 1;
         return nb;
     }();
     return v;
+}
+
+// A persistent grid: at most `blocks` workgroups, every one resident at once.
+template <auto Kernel>
+hipError_t launch_resident(const ScoreArgs& a, int64_t blocks, int ncu, hipStream_t st, Stamp ts)
+{
+    const int64_t cap = (int64_t)ncu * resident_per_cu<Kernel>();
+    const int64_t grid = blocks < cap ? (blocks < 1 ? 1 : blocks) : cap;
+    hipExtLaunchKernelGGL(Kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
+    return hipGetLastError();
 }
 
 // Buffer offsets are 32 bits: key rows up to two units past n must lie below
@@ -1158,15 +1171,11 @@ inline bool use_units(const ScoreArgs& a, int64_t total, int ncu)
 template <typename Keys>
 hipError_t launch_units(const ScoreArgs& a, int64_t total, int ncu, hipStream_t st, Stamp ts)
 {
-    auto go = [&](auto kernel) {
-        const int64_t cap = (int64_t)ncu * resident_per_cu(kernel), want = (total + 3) / 4;
-        hipExtLaunchKernelGGL(kernel, dim3((unsigned)(want < cap ? want : cap)), dim3(256), 0, st, ts.start, ts.stop, 0, a);
-        return hipGetLastError();
-    };
-    return a.G <= 4 ? go(score_units_kernel<Keys, 4>) : go(score_units_kernel<Keys, kMfmaHeads>);
+    const int64_t blocks = (total + 3) / 4;   // a unit per wave
+    return a.G <= 4 ? launch_resident<score_units_kernel<Keys, 4>>(a, blocks, ncu, st, ts)
+                    : launch_resident<score_units_kernel<Keys, kMfmaHeads>>(a, blocks, ncu, st, ts);
 }
 
-// Persistent grid: every workgroup resident at once, each with at least one unit.
 template <int DT, int GC, int OUT>
 hipError_t launch_score_inst(const ScoreArgs& a, int ncu, hipStream_t st, Stamp ts)
 {
@@ -1179,53 +1188,23 @@ hipError_t launch_score_inst(const ScoreArgs& a, int ncu, hipStream_t st, Stamp 
         }
         // int4 sketch, ATTN logits, G >= 4: integer dots on the matrix cores (with fewer heads per
         // key the vector units' dot chains are short and faster)
-        if (a.k8 && a.kbits == 4 && a.G >= 4) {
-            auto kernel = score_tiles_kernel<1, OUT, KeysSketchMfma4<DT>>;
-            const int64_t cap = (int64_t)ncu * resident_per_cu(kernel);
-            const int64_t grid = total < cap ? (total < 1 ? 1 : total) : cap;
-            hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
-            return hipGetLastError();
-        }
-        if (a.k8 && a.kbits == 8 && a.G >= 4) {
-            auto kernel = score_tiles_kernel<1, OUT, KeysSketchMfma8<DT>>;
-            const int64_t cap = (int64_t)ncu * resident_per_cu(kernel);
-            const int64_t grid = total < cap ? (total < 1 ? 1 : total) : cap;
-            hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
-            return hipGetLastError();
-        }
+        if (a.k8 && a.kbits == 4 && a.G >= 4)
+            return launch_resident<score_tiles_kernel<1, OUT, KeysSketchMfma4<DT>>>(a, total, ncu, st, ts);
+        if (a.k8 && a.kbits == 8 && a.G >= 4)
+            return launch_resident<score_tiles_kernel<1, OUT, KeysSketchMfma8<DT>>>(a, total, ncu, st, ts);
         // 16-bit keys, G >= 4: the dots on the matrix cores as well; with at most two units per CU both of
         // a wave's tiles are requested at once (KeysF16MfmaPair; whole steps, one tile at a time -> both:
         // 1 x 8K 25.7 -> 25.1 us per layer; 1 x 16K even, 1 x 32K 31.7 -> 32.2, longer ones within 1 %)
         if (!a.k8 && a.G >= 4) {
-            if (total <= 2ll * ncu && buffer_reaches(a)) {
-                hipExtLaunchKernelGGL((score_tiles_kernel<1, OUT, KeysF16MfmaPair<DT>>), dim3((unsigned)(total < 1 ? 1 : total)),
-                                      dim3(256), 0, st, ts.start, ts.stop, 0, a);
-                return hipGetLastError();
-            }
-            auto kernel = score_tiles_kernel<1, OUT, KeysF16Mfma<DT>>;
-            const int64_t cap = (int64_t)ncu * resident_per_cu(kernel);
-            const int64_t grid = total < cap ? (total < 1 ? 1 : total) : cap;
-            hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
-            return hipGetLastError();
+            if (total <= 2ll * ncu && buffer_reaches(a))
+                return launch_resident<score_tiles_kernel<1, OUT, KeysF16MfmaPair<DT>>>(a, total, ncu, st, ts);
+            return launch_resident<score_tiles_kernel<1, OUT, KeysF16Mfma<DT>>>(a, total, ncu, st, ts);
         }
     }
-    if (a.k8 && a.kbits == 4) {
-        auto kernel = score_tiles_kernel<GC, OUT, KeysSketch<DT, GC, 4>>;
-        const int64_t cap = (int64_t)ncu * resident_per_cu(kernel);
-        const int64_t grid = total < cap ? (total < 1 ? 1 : total) : cap;
-        hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
-    } else if (a.k8) {
-        auto kernel = score_tiles_kernel<GC, OUT, KeysSketch<DT, GC, 8>>;
-        const int64_t cap = (int64_t)ncu * resident_per_cu(kernel);
-        const int64_t grid = total < cap ? (total < 1 ? 1 : total) : cap;
-        hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
-    } else {
-        auto kernel = score_tiles_kernel<GC, OUT, KeysF16<DT, GC>>;
-        const int64_t cap = (int64_t)ncu * resident_per_cu(kernel);
-        const int64_t grid = total < cap ? (total < 1 ? 1 : total) : cap;
-        hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
-    }
-    return hipGetLastError();
+    if (a.k8 && a.kbits == 4)
+        return launch_resident<score_tiles_kernel<GC, OUT, KeysSketch<DT, GC, 4>>>(a, total, ncu, st, ts);
+    if (a.k8) return launch_resident<score_tiles_kernel<GC, OUT, KeysSketch<DT, GC, 8>>>(a, total, ncu, st, ts);
+    return launch_resident<score_tiles_kernel<GC, OUT, KeysF16<DT, GC>>>(a, total, ncu, st, ts);
 }
 
 template <int DT, int OUT>

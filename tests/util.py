@@ -33,3 +33,36 @@ def stream_classes(before, after, n, k, sink=0, recent=0):
                 and (n == pb[2] or nopins))
         out.append(int((pa[0] >> 20) - (pb[0] >> 20)) if used else None)
     return out
+
+
+def kernel_grids(f):
+    """The kernels that f() enqueues on the current stream, in order: their
+    grids (x, y, z) in workgroups, read from the captured graph.  f runs once
+    before the capture and is not replayed."""
+    import ctypes
+
+    class Dim3(ctypes.Structure):
+        _fields_ = [(n, ctypes.c_uint32) for n in "xyz"]
+
+    class Params(ctypes.Structure):   # hipKernelNodeParams
+        _fields_ = [("block", Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", Dim3),
+                    ("args", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
+    with open("/proc/self/maps") as m:   # the HIP runtime that is loaded already
+        hip = ctypes.CDLL(next(l.split()[-1] for l in m if "libamdhip64" in l))
+    f()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        f()
+    graph, n = ctypes.c_void_p(g.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * max(1, n.value))()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    grids = []
+    for node in nodes[:n.value]:
+        kind, p = ctypes.c_int(-1), Params()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        if kind.value == 0:   # a kernel
+            assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+            grids.append((p.grid.x, p.grid.y, p.grid.z))
+    return grids
