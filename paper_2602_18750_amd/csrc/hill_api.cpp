@@ -42,12 +42,15 @@ struct Shape {
 // Workspace regions, in this order, each 256-byte aligned:
 //   logits   ATTN [B,Hq,ld] fp32 | RAW token rows with Hkv > 1: [B,Hkv,ld] fp32 (ld = n rounded up to 4)
 //   part     ATTN [B,Hq,npart] float2 (per 256-token unit);  stats ATTN [B,Hq] float2
+//   sel_list [rows,n] i32; until it is written its last words hold the parts of the first-digit histogram
+//            ([rows,parts,4096+64], where the update counts into several), so that they and the zeroed words
+//            behind them are one range to clear
 //   zeroed   hist1 [rows,4096+64] | hist2 [rows,4096+64] (u32 fine + coarse bins) | hist2x [3,rows,4096+64] (the
 //            streamed selection's further second-digit windows, hist2 continued) -- cleared by the first kernel of
 //            every call that accumulates into them
 //   scount [rows,ceil(n/kUpdChunk),8] u32 | spairs [rows,n] uint2 (key, token) (streamed selection only)
 //   cand_key [rows,n] u32 | cand_n [rows,nchunks] u32 | state [rows] uint4
-//   sel_list [rows,n] i32 | sel_n [rows,nchunks] u32
+//   sel_n [rows,nchunks] u32
 //   slots: attention partials [B,Hq,nslots,D] fp32 and [B,Hq,nslots] float2, nslots =
 //          max(nchunks, splits of the standalone attention)
 // Only the last region depends on k_sel.
@@ -79,6 +82,8 @@ Layout layout_for(const Shape& s, int ksel)
     L.stats = off;
     if (attn) off += align256((size_t)s.B * s.Hq * sizeof(float2));
     L.end_score = off;
+    L.sel_list = off;
+    off += align256(rows * (size_t)s.n * sizeof(int32_t));
     L.zero = off;
     L.hist1 = off;
     L.hist2 = L.hist1 + rows * kHistRow * sizeof(uint32_t);
@@ -99,8 +104,6 @@ Layout layout_for(const Shape& s, int ksel)
     off += align256(rows * L.nchunks * sizeof(uint32_t));
     L.state = off;
     off += align256(rows * sizeof(uint4));
-    L.sel_list = off;
-    off += align256(rows * (size_t)s.n * sizeof(int32_t));
     L.sel_n = off;
     off += align256(rows * L.nchunks * sizeof(uint32_t));
     L.end_topk = off;
@@ -270,12 +273,18 @@ hill_status check_sketch(const Shape& s, const int8_t* k8, const int8_t* k_exp, 
 }
 
 // Parts of the first-digit histogram that the importance update of a step
-// with a refine pass counts into (in the place of the selected lists).
+// with a refine pass counts into (in the place of the selected lists' end).
 int step_hist_parts(const Shape& s)
 {
     const int64_t nup = (s.n + kUpdChunk - 1) / kUpdChunk;
     const int per = update_chunks_per_wg((int64_t)s.B * s.R * nup);
     return hist_parts((nup + per - 1) / per, s.n);
+}
+
+// The first-digit histogram that a step counts into, in `parts` parts.
+uint32_t* step_hist(const Shape& s, const Layout& L, int parts, void* ws)
+{
+    return at<uint32_t>(ws, L.hist1) - (parts > 1 ? (int64_t)s.B * s.R * parts * kHistRow : 0);
 }
 
 // Scoring; if `hist` is given the first selection digit is counted as a side
@@ -291,7 +300,7 @@ hill_status run_score(const hill_desc* d, const Shape& s, const Layout& L, const
     const int64_t nup = (s.n + kUpdChunk - 1) / kUpdChunk, rows = (int64_t)s.B * s.R;
     const int upd_per = s.mode == HILL_SCORE_ATTN ? update_chunks_per_wg(rows * nup) : 1;
     const int parts = stream_prev || s.mode == HILL_SCORE_RAW ? 1 : step_hist_parts(s);
-    uint32_t* hist = with_hist ? at<uint32_t>(ws, parts > 1 ? L.sel_list : L.hist1) : nullptr;
+    uint32_t* hist = with_hist ? step_hist(s, L, parts, ws) : nullptr;
     ScoreArgs a{};
     a.q = static_cast<const uint16_t*>(q);
     a.k = static_cast<const uint16_t*>(k);
@@ -312,12 +321,9 @@ hill_status run_score(const hill_desc* d, const Shape& s, const Layout& L, const
     a.s = sacc;
     a.s_sb = d->s_stride_b;
     a.s_sr = d->s_stride_r;
-    a.zero_ptr = with_hist ? at<uint32_t>(ws, L.zero) : nullptr;
-    a.zero_words = with_hist ? (stream_prev ? L.zero_words_stream : L.zero_words) : 0;
-    if (with_hist && parts > 1) {
-        a.zero2_ptr = hist;
-        a.zero2_words = rows * parts * kHistRow;
-    }
+    a.zero_ptr = hist;
+    if (with_hist)
+        a.zero_words = (at<uint32_t>(ws, L.hist1) - hist) + (stream_prev ? L.zero_words_stream : L.zero_words);
     a.k8 = sk.k8;
     a.k_exp = sk.k_exp;
     a.cap = sk.cap;
@@ -590,7 +596,7 @@ hill_status run_step(const hill_desc* d, const void* q, const void* k, const voi
         r.state_out = state4;   // NULL, or a reset step's fresh bound
         if (s.mode == HILL_SCORE_ATTN && step_hist_parts(s) > 1) {   // as run_score counted it
             r.hist_reps = step_hist_parts(s);
-            r.hist1 = reinterpret_cast<const uint32_t*>(r.sel_list);
+            r.hist1 = step_hist(s, L, r.hist_reps, ws);
         }
         HIP_TRY(launch_topk_refine(r, s.B * s.R, st, stage(e, HILL_STAGE_REFINE)));
         HIP_TRY(launch_topk_emit_attn(r, a, s.dtype, st, stage(e, HILL_STAGE_SELECT)));

@@ -42,8 +42,6 @@ struct ScoreArgs {
     int64_t s_sb, s_sr;
     uint32_t* zero_ptr;      // nullable: words to clear for a later kernel
     int64_t zero_words;
-    uint32_t* zero2_ptr;     // the same, a second range
-    int64_t zero2_words;
     const int8_t* k8;        // nullable: key sketch scored instead of k: int8 codes [B,Hkv,cap,128]
                              //   (kbits 8) or packed int4 codes [B,Hkv,cap,64] bytes (kbits 4)
     const int8_t* k_exp;     //   its per-row exponents [B,Hkv,cap]

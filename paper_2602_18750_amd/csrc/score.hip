@@ -41,14 +41,14 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* p, int64_t wor
         p[i] = 0u;
 }
 
-// The words that a later kernel counts into.
+// The words that a later kernel counts into (one range: a second one in the
+// arguments cost every sketch scan two registers).
 __device__ __forceinline__ void clear_words(const ScoreArgs& a)
 {
-    const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
-    if (a.zero_ptr)
-        for (int64_t i = i0; i < a.zero_words; i += step) a.zero_ptr[i] = 0u;
-    if (a.zero2_ptr)
-        for (int64_t i = i0; i < a.zero2_words; i += step) a.zero2_ptr[i] = 0u;
+    if (a.zero_ptr) {
+        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.zero_words; i += (int64_t)gridDim.x * 256)
+            a.zero_ptr[i] = 0u;
+    }
 }
 
 struct TileCoord {
@@ -137,16 +137,17 @@ struct KeysF16 {
 // changes: wave w casts heads w, w+4, ... into LDS (group_query), and every
 // wave reads its slices from there (query).  The dot product is exact in
 // int32 (|sum| < 2^24) and scaled by 2^(e_q + e_k).
-struct QueryLds {
-    int8_t q8[kMaxGroup][kHeadDim];
-    int eq[kMaxGroup];
+template <int HEADS>
+struct QueryCasts {
+    int8_t q8[HEADS][kHeadDim];
+    int eq[HEADS];
 };
+using QueryLds = QueryCasts<kMaxGroup>;
 
 // The queries of a key-sketch scan: cast once per (b, g) into LDS.
-template <int DT>
+template <int DT, typename QL = QueryLds>
 struct SketchQuery {
-    int8_t (*q8c)[kHeadDim] = nullptr;   // the casts and their exponents in LDS
-    int* eqc = nullptr;
+    QL* ql = nullptr;
     int q_tag = -1;
 
     // The raw query words of the group's first heads (wave w: heads w and
@@ -177,8 +178,8 @@ struct SketchQuery {
         const int e = sketch_exponent<127>(wave_max(fmaxf(fabsf(x0), fabsf(x1))));
         const uint32_t c2 =
             ((uint32_t)sketch_code<127>(x0, e) & 0xffu) | (((uint32_t)sketch_code<127>(x1, e) & 0xffu) << 8);
-        *reinterpret_cast<uint16_t*>(&q8c[h][2 * lane]) = (uint16_t)c2;
-        if (lane == 0) eqc[h] = e;
+        *reinterpret_cast<uint16_t*>(&ql->q8[h][2 * lane]) = (uint16_t)c2;
+        if (lane == 0) ql->eq[h] = e;
     }
 
     // Casts the G queries of group (b, g) into LDS; wave w takes heads w, w+4, ...
@@ -204,8 +205,7 @@ struct KeysSketch : SketchQuery<DT> {
     static constexpr bool kMfmaSplit = false;
     static constexpr int kRowBytes = kHeadDim * BITS / 8;
     using Codes = typename std::conditional<BITS == 8, uint4, uint2>::type;
-    using SketchQuery<DT>::q8c;
-    using SketchQuery<DT>::eqc;
+    using SketchQuery<DT>::ql;
     using SketchQuery<DT>::q_tag;
     Codes kr[kSlots][kRowsPerLane];
     uint32_t ek4[kSlots];   // exponents of the 4 rows, one byte each
@@ -239,8 +239,8 @@ struct KeysSketch : SketchQuery<DT> {
         if (tag == q_tag) return;
 #pragma unroll
         for (int hh = 0; hh < GC; ++hh) {
-            q8[hh] = *reinterpret_cast<const uint4*>(&q8c[hc + hh][16 * l8]);
-            eq[hh] = eqc[hc + hh];
+            q8[hh] = *reinterpret_cast<const uint4*>(&ql->q8[hc + hh][16 * l8]);
+            eq[hh] = ql->eq[hc + hh];
             if constexpr (BITS == 4) {
                 const int ones = 0x01010101;
                 int sq = __builtin_amdgcn_sdot4((int)q8[hh].x, ones, 0, false);
@@ -250,7 +250,7 @@ struct KeysSketch : SketchQuery<DT> {
                 qbias[hh] = 8 * sq;
             }
         }
-        eq_lane = eqc[hc + (l8 < GC ? l8 : 0)];   // from LDS: a register-array pick would be indexed
+        eq_lane = ql->eq[hc + (l8 < GC ? l8 : 0)];   // from LDS: a register-array pick would be indexed
         q_tag = tag;
     }
 
@@ -393,15 +393,14 @@ struct KeysF16Mfma {
 // v_mfma_i32_16x16x32_i8 (its low and high 8 codes).  The integer halves are
 // joined by one DPP add and scaled by 2^(e_q + e_k) as on the vector units:
 // the logits are the same exact values.
-template <int DT>
-struct KeysSketchMfma8 : SketchQuery<DT> {
+template <int DT, typename QL = QueryLds>
+struct KeysSketchMfma8 : SketchQuery<DT, QL> {
     static constexpr int kSlots = 2;
     static constexpr bool kGroupQuery = true;
     static constexpr bool kIntDot = true;
     static constexpr bool kMfmaSplit = true;
-    using SketchQuery<DT>::q8c;
-    using SketchQuery<DT>::eqc;
-    using SketchQuery<DT>::q_tag;
+    using SketchQuery<DT, QL>::ql;
+    using SketchQuery<DT, QL>::q_tag;
     uint4 kr[kSlots][4];       // [tile][group]: the lane's 16 code bytes
     uint32_t ek4[kSlots];      // exponents of the lane's 4 output tokens
     uint64_t qb[2];            // query operand of the two MFMAs (column l % 16)
@@ -434,8 +433,8 @@ struct KeysSketchMfma8 : SketchQuery<DT> {
         uint4 x = make_uint4(0u, 0u, 0u, 0u);
         eq_lane = 0;
         if (h < a.G) {
-            x = *reinterpret_cast<const uint4*>(&q8c[h][(2 * (lane >> 4) + (col & 1)) * 16]);
-            eq_lane = eqc[h];
+            x = *reinterpret_cast<const uint4*>(&ql->q8[h][(2 * (lane >> 4) + (col & 1)) * 16]);
+            eq_lane = ql->eq[h];
         }
         qb[0] = (uint64_t)x.x | ((uint64_t)x.y << 32);
         qb[1] = (uint64_t)x.z | ((uint64_t)x.w << 32);
@@ -477,16 +476,15 @@ struct KeysSketchMfma8 : SketchQuery<DT> {
 // exchange of two sums per group then leaves 4 consecutive tokens per lane
 // (even lanes 8q .. +3, odd lanes 8q + 4 .. +7), scaled by 2^(e_q + e_k) as on
 // the vector units: the same exact logits.
-template <int DT>
-struct KeysSketchMfma4 : SketchQuery<DT> {
+template <int DT, typename QL = QueryLds>
+struct KeysSketchMfma4 : SketchQuery<DT, QL> {
     static constexpr int kSlots = 2;
     static constexpr bool kGroupQuery = true;
     static constexpr bool kIntDot = true;
     static constexpr bool kMfmaSplit = true;
     static constexpr int kRowBytes = kHeadDim / 2;
-    using SketchQuery<DT>::q8c;
-    using SketchQuery<DT>::eqc;
-    using SketchQuery<DT>::q_tag;
+    using SketchQuery<DT, QL>::ql;
+    using SketchQuery<DT, QL>::q_tag;
     uint2 kr[kSlots][4];       // [tile][group]: the lane's 8 code bytes (two words)
     uint32_t ek4[kSlots];      // exponents of the lane's 4 output tokens
     uint64_t qb[2];            // query operand of the two MFMAs (column l % 16)
@@ -519,8 +517,8 @@ struct KeysSketchMfma4 : SketchQuery<DT> {
         eq_lane = 0;
         if (h < a.G) {
             // codes of the lane's key bytes: 2 per byte, at 2 * (16p' + 8(c & 1) + 32(c >> 1))
-            x = *reinterpret_cast<const uint4*>(&q8c[h][32 * (col & 1) + 16 * (qc & 1) + 64 * (qc >> 1)]);
-            eq_lane = eqc[h];
+            x = *reinterpret_cast<const uint4*>(&ql->q8[h][32 * (col & 1) + 16 * (qc & 1) + 64 * (qc >> 1)]);
+            eq_lane = ql->eq[h];
         }
         qb[0] = (uint64_t)x.x | ((uint64_t)x.y << 32);
         qb[1] = (uint64_t)x.z | ((uint64_t)x.w << 32);
@@ -763,8 +761,7 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(ScoreArgs a)
             ks.template load<0>(a, c0, rg, l8);
             ks.template load<1>(a, c1, rg, l8);
             if (fresh) {
-                ks.q8c = qlds.q8;
-                ks.eqc = qlds.eq;
+                ks.ql = &qlds;
                 ks.group_query(a, bg / a.Hkv, bg % a.Hkv, wv, lane);
                 __syncthreads();
                 cur_bg = bg;
@@ -932,10 +929,14 @@ struct KeysF16MfmaPair : KeysF16Mfma<DT> {
     }
 };
 
-// The sketch sources: KEYS = KeysSketchMfma8<DT> or KeysSketchMfma4<DT>, whose
-// group's queries are cast into the wave's own LDS.
-template <int DT, typename KEYS, int BITS>
-struct UnitKeysSketch : KEYS {
+// The sketch sources: KeysSketchMfma8 / KeysSketchMfma4, whose group's queries
+// (at most HB heads) are cast into the wave's own LDS.
+template <int DT, int BITS, int HB>
+using MfmaSketchKeys = typename std::conditional<BITS == 8, KeysSketchMfma8<DT, QueryCasts<HB>>,
+                                                 KeysSketchMfma4<DT, QueryCasts<HB>>>::type;
+
+template <int DT, int BITS, int HB>
+struct UnitKeysSketch : MfmaSketchKeys<DT, BITS, HB> {
     static constexpr int kDepth = 4;
     static constexpr bool kCast = true;
     static constexpr int kRowBytes = kHeadDim * BITS / 8;
@@ -1036,8 +1037,7 @@ template <typename Keys, int HB>
 __global__ __launch_bounds__(256, 4) void score_units_kernel(ScoreArgs a)
 {
     __shared__ float unit_lds[4][HB][kUnitTokens];
-    __shared__ typename std::conditional<Keys::kCast, int8_t[4][HB][kHeadDim], int>::type q8_lds;
-    __shared__ int eq_lds[4][HB];
+    __shared__ typename std::conditional<Keys::kCast, QueryCasts<HB>[4], int>::type q_lds;
     constexpr int kD = Keys::kDepth;
     static_assert(kUnitTiles % kD == 0 && kUnitTokens == 4 * 64, "slots repeat per unit; 16 bytes per lane and head");
     const int lane = threadIdx.x & 63;
@@ -1049,8 +1049,7 @@ __global__ __launch_bounds__(256, 4) void score_units_kernel(ScoreArgs a)
     Keys ks;
     ks.init(a, lane);
     if constexpr (Keys::kCast) {
-        ks.q8c = q8_lds[wv];
-        ks.eqc = eq_lds[wv];
+        ks.ql = &q_lds[wv];
     }
     const int h = (lane & 15) >> 1;
     const bool live = h < a.G;
@@ -1168,12 +1167,13 @@ inline bool use_units(const ScoreArgs& a, int64_t total, int ncu)
     return a.G >= 4 && total >= 16ll * ncu && buffer_reaches(a);
 }
 
-template <typename Keys>
+template <int DT, int HB>
 hipError_t launch_units(const ScoreArgs& a, int64_t total, int ncu, hipStream_t st, Stamp ts)
 {
     const int64_t blocks = (total + 3) / 4;   // a unit per wave
-    return a.G <= 4 ? launch_resident<score_units_kernel<Keys, 4>>(a, blocks, ncu, st, ts)
-                    : launch_resident<score_units_kernel<Keys, kMfmaHeads>>(a, blocks, ncu, st, ts);
+    if (!a.k8) return launch_resident<score_units_kernel<UnitKeysF16<DT>, HB>>(a, blocks, ncu, st, ts);
+    return a.kbits == 4 ? launch_resident<score_units_kernel<UnitKeysSketch<DT, 4, HB>, HB>>(a, blocks, ncu, st, ts)
+                        : launch_resident<score_units_kernel<UnitKeysSketch<DT, 8, HB>, HB>>(a, blocks, ncu, st, ts);
 }
 
 template <int DT, int GC, int OUT>
@@ -1181,11 +1181,8 @@ hipError_t launch_score_inst(const ScoreArgs& a, int ncu, hipStream_t st, Stamp 
 {
     const int64_t total = (int64_t)a.B * a.Hkv * a.npart;
     if constexpr (OUT == kOutLogits) {
-        if (use_units(a, total, ncu)) {
-            if (a.k8 && a.kbits == 4) return launch_units<UnitKeysSketch<DT, KeysSketchMfma4<DT>, 4>>(a, total, ncu, st, ts);
-            if (a.k8) return launch_units<UnitKeysSketch<DT, KeysSketchMfma8<DT>, 8>>(a, total, ncu, st, ts);
-            return launch_units<UnitKeysF16<DT>>(a, total, ncu, st, ts);
-        }
+        if (use_units(a, total, ncu))
+            return a.G <= 4 ? launch_units<DT, 4>(a, total, ncu, st, ts) : launch_units<DT, kMfmaHeads>(a, total, ncu, st, ts);
         // int4 sketch, ATTN logits, G >= 4: integer dots on the matrix cores (with fewer heads per
         // key the vector units' dot chains are short and faster)
         if (a.k8 && a.kbits == 4 && a.G >= 4)

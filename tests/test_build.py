@@ -26,3 +26,12 @@ def test_every_kernel_is_reported(report):
 def test_no_kernel_uses_scratch(report):
     bad = [(r[0], r[1], r[3]) for r in report if r[3] != "scratch=0"]
     assert not bad, bad
+
+
+def test_resident_scan_workgroups(report):
+    """The scans hide memory latency by the workgroups (of one wave per SIMD)
+    that fit a CU together: 16-bit matrix-core 6, int8 5, int4 4."""
+    want = {"KeysF16MfmaILi": 6, "KeysSketchMfma8ILi": 5, "KeysSketchMfma4ILi": 4}
+    for name, n in want.items():
+        got = [int(r[4].split("=")[1]) for r in report if "score_tiles_kernel" in r[1] and name in r[1]]
+        assert len(got) == 2 and min(got) >= n, (name, got)
