@@ -736,7 +736,8 @@ def _counter_rows(directory: str, counter: str, name_part: str, steady: bool = F
 
 
 STEP_SOURCES = [os.path.join(ROOT, "paper_2602_18750_amd", "csrc", f)
-                for f in ("update.hip", "topk.hip", "attn_device.h", "hill_device.h", "hill_internal.h")]
+                for f in ("update.hip", "topk.hip", "emit_logits.hip", "topk_device.h", "attn_device.h", "hill_device.h",
+                          "hill_internal.h")]
 STEP_COUNTERS_FILE = os.path.join(ROOT, "profiles", "step_kernels_counters.json")
 
 
@@ -788,7 +789,7 @@ def make_step_counters(directory: str, command: str):
     w = W.WORKLOADS[COUNTERS_WORKLOAD]
     alg = step_algorithmic_bytes(w.batch, w.n_q_heads, w.n_kv_heads, w.head_dim, w.n_tokens, w.k_sel)
     names = {"update_attn": r"update_attn_kernel",
-             "topk_emit": r"topk_emit_kernel<1, 4, true, true, true, false, true>",
+             "topk_emit": r"topk_emit_kernel<1, 4, true, true, true, false, true, false>",
              "merge_write": r"merge_write_kernel"}
     rec = {"workload": w.name, "source_sha256": step_sources_sha(), "fetch_factor": round(ff, 4),
            "write_factor": round(wf, 4), "kernels": {}, "command": command}
@@ -876,7 +877,7 @@ def _steady_state(path: str, directory: str):
     while i + 3 < len(rows):
         n = names[i:i + 4]
         if (n[0].startswith("hill::score_tiles_kernel") and "KeysF16" in n[0] and n[1] == "hill::update_attn_kernel"
-                and n[2].startswith("hill::topk_emit_kernel") and n[2].count("true") >= 2
+                and re.match(r"hill::topk_emit_kernel<\d, \d, true, true\b", n[2])   # streamed
                 and n[3] == "hill::merge_write_kernel"):
             seqs.append(rows[i:i + 4])
             i += 4

@@ -15,7 +15,7 @@ namespace hill {
 
 namespace {
 
-template <int DT, int GC>
+template <int DT, int GC, bool MASK>
 __global__ __launch_bounds__(256) void attn_split_kernel(AttnArgs a)
 {
     __shared__ AttnLds<GC> sh;
@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void attn_split_kernel(AttnArgs a)
     const int t1 = min(t0 + a.per_split, a.ksel);
     for (int hc = 0; hc < a.G; hc += GC) {
         uint4 qv[GC];
-        load_queries<GC>(a, b, g, hc, qv);
+        load_queries<GC, MASK>(a, b, g, hc, qv);
         AttnAcc<GC> acc;
         attn_begin<GC>(acc, sh);
         for (int tb = t0; tb < t1; tb += kAttnBlock) {
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256) void attn_split_kernel(AttnArgs a)
             __syncthreads();
             attn_block<DT, GC>(a, b, g, qv, cnt, acc, sh);
         }
-        attn_finish<GC>(a, b, g, hc, acc, split, a.nsplit, sh);
+        attn_finish<GC, MASK>(a, b, g, hc, acc, split, a.nsplit, sh);
     }
 }
 
@@ -51,12 +51,14 @@ __global__ __launch_bounds__(kHeadDim) void attn_combine_kernel(AttnArgs a)
 template <int DT>
 hipError_t launch_attn_dt(const AttnArgs& a, dim3 grid, hipStream_t st)
 {
+    const bool mask = masked_pass(a.G);
+    auto kernel = attn_split_kernel<DT, 1, false>;
     switch (heads_per_pass(a.G)) {
-    case 8: hipLaunchKernelGGL((attn_split_kernel<DT, 8>), grid, dim3(256), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((attn_split_kernel<DT, 4>), grid, dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((attn_split_kernel<DT, 2>), grid, dim3(256), 0, st, a); break;
-    default: hipLaunchKernelGGL((attn_split_kernel<DT, 1>), grid, dim3(256), 0, st, a); break;
+    case 8: kernel = mask ? attn_split_kernel<DT, 8, true> : attn_split_kernel<DT, 8, false>; break;
+    case 4: kernel = mask ? attn_split_kernel<DT, 4, true> : attn_split_kernel<DT, 4, false>; break;
+    case 2: kernel = attn_split_kernel<DT, 2, false>; break;
     }
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

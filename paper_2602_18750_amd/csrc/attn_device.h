@@ -49,17 +49,20 @@ struct AttnLds {
 // the fewest passes, the last one with its heads past G masked (they repeat
 // head G-1 and are not stored).  The rows are read once per pass: the emit
 // kernel of a 3 x 20K step with 7 heads per KV head takes 11.2 us in one masked
-// pass, 22.0 head by head; 2 x 32K with 5 heads 12.1 and 20.6.
+// pass, 22.0 head by head; 2 x 32K with 5 heads 12.1 and 20.6.  Whether there
+// are masked heads is a compile-time choice (MASK): groups of 1, 2, 4 and
+// multiples of 8 heads need no clamps and tests.
 inline int heads_per_pass(int G) { return G > 4 ? 8 : G > 2 ? 4 : G; }
+inline bool masked_pass(int G) { return G % heads_per_pass(G) != 0; }
 
 // This lane's 8 query elements of heads g*G+hc .. +GC (16-lane row layout).
-template <int GC>
+template <int GC, bool MASK>
 __device__ __forceinline__ void load_queries(const AttnArgs& a, int b, int g, int hc, uint4 (&qv)[GC])
 {
     const int l16 = threadIdx.x & 15;
 #pragma unroll
     for (int hh = 0; hh < GC; ++hh) {
-        const int h = g * a.G + min(hc + hh, a.G - 1);
+        const int h = g * a.G + (MASK ? min(hc + hh, a.G - 1) : hc + hh);
         qv[hh] = *reinterpret_cast<const uint4*>(a.q + (int64_t)b * a.q_sb + (int64_t)h * a.q_sh + l16 * 8);
     }
 }
@@ -353,7 +356,7 @@ __device__ __forceinline__ void attn_block_logits(const AttnArgs& a, int b, int 
 // Adds the four waves' outputs and writes the partial (m, l, o[D]) of heads
 // g*G+hc .. +GC to slot `slot` of `nslots`.  An empty list gives m = -inf,
 // l = 0, o = 0 (weight 0 in the merge).  Every thread must call this.
-template <int GC>
+template <int GC, bool MASK>
 __device__ __forceinline__ void attn_finish(const AttnArgs& a, int b, int g, int hc, const AttnAcc<GC>& acc, int slot,
                                             int nslots, AttnLds<GC>& sh)
 {
@@ -366,7 +369,7 @@ __device__ __forceinline__ void attn_finish(const AttnArgs& a, int b, int g, int
         const int hh = e / kHeadDim, d = e % kHeadDim;
         const float o = ((sh.o[0][hh][d] + sh.o[1][hh][d]) + sh.o[2][hh][d]) + sh.o[3][hh][d];
         const int64_t pi = ((int64_t)b * a.Hq + g * a.G + hc + hh) * nslots + slot;
-        const bool live = hc + hh < a.G;   // not a masked head
+        const bool live = !MASK || hc + hh < a.G;   // not a masked head
         if (live) a.part_o[pi * kHeadDim + d] = o;
         if (live && d == 0) a.part_ml[pi] = make_float2(sh.mrun[hh], sh.lrun[hh]);
     }

@@ -401,7 +401,6 @@ RefineArgs refine_args(const hill_desc* d, const Shape& s, const Layout& L, cons
     r.k = ksel;
     r.nchunks = L.nchunks;
     r.hist1 = at<uint32_t>(ws, L.hist1);
-    r.hist_reps = 1;
     r.hist2 = at<uint32_t>(ws, L.hist2);
     r.cand_key = at<uint32_t>(ws, L.cand_key);
     r.cand_n = at<uint32_t>(ws, L.cand_n);
@@ -427,7 +426,7 @@ hill_status run_select(const hill_desc* d, const Shape& s, const Layout& L, cons
     HIP_TRY(launch_fill_zero(at<uint32_t>(ws, L.zero), L.zero_words, st));
     HIP_TRY(launch_topk_hist(sacc, d->s_stride_b, d->s_stride_r, s.B, s.R, s.n, s.pin_lo, s.pin_hi,
                              at<uint32_t>(ws, L.hist1), st));
-    HIP_TRY(launch_topk_refine(r, s.B * s.R, st));
+    HIP_TRY(launch_topk_refine(r, s.B * s.R, 1, st));
     HIP_TRY(launch_topk_emit_indices(r, s.B * s.R, idx, val, st));
     return HILL_OK;
 }
@@ -594,11 +593,9 @@ hill_status run_step(const hill_desc* d, const void* q, const void* k, const voi
         HIP_TRY(launch_topk_emit_attn_stream(r, a, s.dtype, st, stage(e, HILL_STAGE_SELECT)));
     } else {
         r.state_out = state4;   // NULL, or a reset step's fresh bound
-        if (s.mode == HILL_SCORE_ATTN && step_hist_parts(s) > 1) {   // as run_score counted it
-            r.hist_reps = step_hist_parts(s);
-            r.hist1 = step_hist(s, L, r.hist_reps, ws);
-        }
-        HIP_TRY(launch_topk_refine(r, s.B * s.R, st, stage(e, HILL_STAGE_REFINE)));
+        const int parts = s.mode == HILL_SCORE_ATTN ? step_hist_parts(s) : 1;   // as run_score counted it
+        r.hist1 = step_hist(s, L, parts, ws);
+        HIP_TRY(launch_topk_refine(r, s.B * s.R, parts, st, stage(e, HILL_STAGE_REFINE)));
         HIP_TRY(launch_topk_emit_attn(r, a, s.dtype, st, stage(e, HILL_STAGE_SELECT)));
     }
     HIP_TRY(launch_merge_write(r, a, idx_out, s.B * s.R, st, stage(e, HILL_STAGE_MERGE)));
@@ -803,7 +800,6 @@ hill_status hill_bkp_update(const hill_bkp_desc* d, const int32_t* idx, int32_t 
         r.k = a.f;
         r.nchunks = L.nchunks;
         r.hist1 = at<uint32_t>(ws, L.hist1);
-        r.hist_reps = 1;
         r.hist2 = at<uint32_t>(ws, L.hist2);
         r.cand_key = at<uint32_t>(ws, L.cand_key);
         r.cand_n = at<uint32_t>(ws, L.cand_n);
@@ -812,7 +808,7 @@ hill_status hill_bkp_update(const hill_bkp_desc* d, const int32_t* idx, int32_t 
         r.sel_n = at<uint32_t>(ws, L.sel_n);
         r.pin_lo = 0;
         r.pin_hi = n;
-        HIP_TRY(launch_topk_refine(r, rows, st));
+        HIP_TRY(launch_topk_refine(r, rows, 1, st));
         HIP_TRY(launch_topk_emit_lists(r, rows, st));
     }
     HIP_TRY(launch_bkp_lists(a, rows, st));

@@ -73,7 +73,6 @@ struct UpdateArgs {
     const float2* stats;     // ATTN: [B,Hq] (max, 1/sum) in the exp2 domain, or null: then
     const float2* part;      //   the kernel reduces the [B,Hq,npart] unit partials itself
     int npart;
-    int per;                 // update_attn: consecutive kUpdChunk-token chunks per workgroup
     int tph;                 // update_attn: threads per head in the reduction (kUpdThreads / heads per row)
     float inv_tph;           //   and 1 / tph
     float* s;
@@ -81,7 +80,7 @@ struct UpdateArgs {
     int B, Hq, Hkv, G, R, n;
     float s2;
     uint32_t* hist;          // nullable: [B*R, hist_reps, kHistRow] first-digit counts (fine, coarse) in
-    int hist_reps;           //   hist_reps parts, workgroup i counting into part i % hist_reps
+                             //   hist_reps parts, workgroup i counting into part i % hist_reps
     int pin_lo, pin_hi;      // tokens outside [pin_lo, pin_hi) count with the largest key (lo == hi: all)
     // streamed selection (nullable prev): candidates above the previous step's threshold
     const uint4* prev;       // [B*R, 2] caller's state (see StreamState)
@@ -92,6 +91,10 @@ struct UpdateArgs {
     uint32_t* hist2;         // [kStreamBins, B*R, kHistRow] second-digit counts of the keys in first-digit
                              //   bin d0 + w (w = 0: the selection's usual second-digit histogram)
     int k;                   // this step's budget
+    // last, where they leave the arguments above in the places from which the kernels' openings fetch them
+    // with few wide loads
+    int hist_reps;
+    int per;                 // update_attn: consecutive kUpdChunk-token chunks per workgroup
 };
 
 // A streamed step over more tokens than this (rows of all sequences together)
@@ -166,8 +169,9 @@ struct RefineArgs {
     const float* s;
     int64_t s_sb, s_sr;
     int R, n, k, nchunks;
-    const uint32_t* hist1;   // [rows, hist_reps, kHistRow] first-digit counts (bits 31..20; coarse: bits 31..26)
-    int hist_reps;           //   in hist_reps parts to be added (refine pass; 1 where no refine pass runs)
+    const uint32_t* hist1;   // [rows, kHistRow] first-digit counts (bits 31..20; coarse: bits 31..26); for the
+                             //   refine pass [rows, parts, kHistRow] in parts to be added (an argument of its own:
+                             //   a member for it cost topk_emit its wide argument loads and scalar registers)
     uint32_t* hist2;         // [rows, kHistRow] second-digit counts (bits 19..8; coarse: bits 19..14), zeroed before
     uint32_t* cand_key;      // [rows, n] keys inside the first-digit bin, chunk c at offset c*kSelChunk
     uint32_t* cand_n;        // [rows, nchunks]
@@ -322,7 +326,7 @@ hipError_t launch_update_attn(const UpdateArgs& a, hipStream_t st, Stamp ts = {}
 hipError_t launch_update_raw_groups(const UpdateArgs& a, hipStream_t st, Stamp ts = {});
 hipError_t launch_topk_hist(const float* s, int64_t s_sb, int64_t s_sr, int B, int R, int n, int pin_lo,
                             int pin_hi, uint32_t* hist, hipStream_t st, Stamp ts = {});
-hipError_t launch_topk_refine(const RefineArgs& a, int rows, hipStream_t st, Stamp ts = {});
+hipError_t launch_topk_refine(const RefineArgs& a, int rows, int parts, hipStream_t st, Stamp ts = {});
 // Selects per chunk and writes the ordered indices (and values, if val).
 hipError_t launch_topk_emit_indices(const RefineArgs& r, int rows, int32_t* idx, float* val, hipStream_t st,
                                     Stamp ts = {});
@@ -338,6 +342,10 @@ hipError_t launch_topk_emit_lists(const RefineArgs& r, int rows, hipStream_t st)
 // slots).  launch_merge_write then merges the partials into at.out and
 // writes the ordered indices.
 hipError_t launch_topk_emit_attn(const RefineArgs& r, const AttnArgs& at, int dtype, hipStream_t st, Stamp ts = {});
+hipError_t launch_emit_logits(const RefineArgs& r, const AttnArgs& at, int dtype, bool streamed, hipStream_t st,
+                              Stamp ts);
+hipError_t launch_emit_gather(const RefineArgs& r, const AttnArgs& at, int dtype, bool streamed, hipStream_t st,
+                              Stamp ts);
 hipError_t launch_merge_write(const RefineArgs& r, const AttnArgs& at, int32_t* idx, int rows, hipStream_t st,
                               Stamp ts = {});
 // Short rows end their step in one launch (row_attend in row.hip) after the

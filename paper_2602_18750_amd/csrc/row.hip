@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kRowThreads) void row_attend_kernel(RefineArgs r, A
         } else {
             // 16-lane row groups: K rows of entries rg, rg + 64, ...
             uint4 qv[GC];
-            load_queries<GC>(at, b, g, hc, qv);
+            load_queries<GC, true>(at, b, g, hc, qv);
             const int rg = tid >> 4, l16 = tid & 15;
             const uint16_t* kb = at.k + (int64_t)b * at.k_sb + (int64_t)g * at.k_sh + l16 * 8;
             const uint16_t* khot = TIER ? at.k_hot + (int64_t)b * at.hk_sb + (int64_t)g * at.hk_sh + l16 * 8 : kb;

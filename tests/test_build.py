@@ -23,6 +23,15 @@ def test_every_kernel_is_reported(report):
         assert k in names, k
 
 
+def test_exact_groups_have_kernels_without_masks(report):
+    """Groups of 1, 2, 4 and 8 heads per pass select and attend without the
+    clamps and tests of a masked pass (the last template argument)."""
+    for gc in (1, 2, 4, 8):
+        for name in ("topk_emit_kernelILi1ELi%dELb1E" % gc, "attn_split_kernelILi1ELi%dE" % gc):
+            last = {r[1].split("EEEv")[0][-3:] for r in report if name in r[1]}
+            assert last == ({"Lb0", "Lb1"} if gc >= 4 else {"Lb0"}), (name, last)
+
+
 def test_no_kernel_uses_scratch(report):
     bad = [(r[0], r[1], r[3]) for r in report if r[3] != "scratch=0"]
     assert not bad, bad
