@@ -161,6 +161,36 @@ __device__ __forceinline__ int sketch_code(float x, int e)
     return (int)fminf(fmaxf(r, -(float)QMAX), (float)QMAX);
 }
 
+// Max and sum over lanes l, l ^ 16, l ^ 32, l ^ 48 by row swaps on the vector
+// unit (the LDS exchange of __shfl_xor takes a round trip each).
+__device__ __forceinline__ float max_x16_x32(float v)
+{
+    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// Sums of two values by one swap: lanes whose bit 5 (16: bit 4) is clear get
+// a's sum over lanes l, l ^ 32 (l ^ 16), the others b's.
+__device__ __forceinline__ float sum2_x32(float a, float b)
+{
+    auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+__device__ __forceinline__ float sum2_x16(float a, float b)
+{
+    auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+__device__ __forceinline__ float sum_x16_x32(float v)
+{
+    v = sum2_x16(v, v);
+    return sum2_x32(v, v);
+}
+
 // Sum over each aligned group of 16 lanes; every lane of the group gets the sum.
 // quad_perm[1,0,3,2], quad_perm[2,3,0,1], row_half_mirror, row_mirror.
 __device__ __forceinline__ float sum16(float v)

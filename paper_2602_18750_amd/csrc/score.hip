@@ -817,24 +817,6 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(ScoreArgs a)
 // slower again (33 us).  One contiguous range of units per wave instead of
 // strided ones: 205 against 194 us.
 
-// Max and sum over lanes l, l ^ 16, l ^ 32, l ^ 48 by row swaps on the vector
-// unit (the LDS exchange of __shfl_xor takes a round trip each).
-__device__ __forceinline__ float max_x16_x32(float v)
-{
-    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-
-__device__ __forceinline__ float sum_x16_x32(float v)
-{
-    auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-    auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
-
 constexpr int kUnitTokens = kUnitTiles * kScoreTile;
 constexpr int kAuxNt = 2;    // buffer cache policy: non-temporal
 constexpr int kAuxSc1 = 16;  // buffer cache policy: device scope, i.e. stores written through
