@@ -248,9 +248,9 @@ HILL_API hill_status hill_step_profiled(const hill_desc* d, const void* q, const
  * threshold bounds the next one only loosely) and after S was changed
  * outside these calls; results are the same either way.  ATTN score mode
  * only (HILL_ERR_UNSUPPORTED otherwise).  Calls over more than 196608 tokens
- * (batch * rows * n_tokens) always select that way.  ev: as
- * hill_step_profiled (otherwise, without HILL_STREAM_RESET, the REFINE stage
- * does not run). */
+ * (batch * n_tokens), or 262144 where every KV head has a row of its own (batch
+ * * rows * n_tokens), always select that way.  ev: as hill_step_profiled
+ * (otherwise, without HILL_STREAM_RESET, the REFINE stage does not run). */
 #define HILL_STREAM_RESET 1u
 HILL_API hill_status hill_step_streamed(const hill_desc* d, const void* q, const void* k, const void* v, float* s,
                                uint32_t* state, uint32_t flags, int32_t k_sel, int32_t* idx_out, float* out,

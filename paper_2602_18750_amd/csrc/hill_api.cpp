@@ -564,7 +564,7 @@ hill_status run_step(const hill_desc* d, const void* q, const void* k, const voi
     const bool short_row = row_step(s.B, s.Hkv, s.n, k_sel, kgather);
     // a reset step, and a streamed one over very many tokens, selects through the refine pass and only
     // writes the bound
-    if (state4 && (int64_t)s.B * s.R * s.n > kStreamMaxTokens) stream_reset = true;
+    if (state4 && !stream_selects(s.B, s.Hkv, s.R, s.n)) stream_reset = true;
     HILL_TRY(run_score(d, s, L, q, k, sk, s_acc, ws, !short_row, st, e, stream_reset || short_row ? nullptr : state4,
                        k_sel));
     RefineArgs r = refine_args(d, s, L, s_acc, k_sel, ws);

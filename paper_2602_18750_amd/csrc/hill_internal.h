@@ -100,11 +100,24 @@ struct UpdateArgs {
 // A streamed step over more tokens than this (rows of all sequences together)
 // selects through the refine pass, as a reset step does, and writes the bound
 // from it: its results are the same, and the walks of long pair lists in every
-// workgroup cost more than the refine launch.  Whole steps, streamed -> refine
-// (us): 4 x 64K 152.4 -> 149.4, 32 x 8K 149.8 -> 147.0, 16 x 30K 256.7 ->
-// 247.0, 4 x 131K 277 -> 271; on the other side 1 x 131K 102.1 and 104.4 per
-// layer, 4 x 32K 84.1 and 85.3, 1 x 32K 31.8 and 35.6.
+// workgroup cost more than the refine launch.  Several KV heads' workgroups
+// walk a token row, one KV head's a KV-head row (or a token row of one KV
+// head).  Whole steps, streamed -> refine (us), 8 KV heads unless said:
+//   token rows: 4 x 64K 152.4 -> 149.4, 8 x 32K 144.9 -> 142.3, 32 x 8K 149.8
+//     -> 147.0, 16 x 30K 256.7 -> 247.0, 4 x 131K 277 -> 271; on the other side
+//     1 x 131K 102.1 and 104.4 per layer, 4 x 32K 84.1 and 85.3, 1 x 32K 31.8
+//     and 35.6
+//   KV-head rows: 8 x 4500 92.9 -> 91.2, 4 x 10K 93.9 -> 92.6, 2 x 20K even, 5 x
+//     20K with 4 KV heads 126.4 -> 114.5, 3 x 20K 116.7 -> 114.4, 1 x 64K 124.7
+//     -> 122.4; on the other side 4 x 8K 82.8 and 85.1, 1 x 32K 165.0 and 170.9
+//     (four layers), 3 x 20K with 4 KV heads 84.1 and 87.4, with one 4 x 64K 95.2
+//     and 97.7, 2 x 131K 118.0 and 122.5
 constexpr int64_t kStreamMaxTokens = 192 << 10;
+constexpr int64_t kStreamMaxTokensPerHead = 256 << 10;
+inline bool stream_selects(int B, int Hkv, int R, int n)
+{
+    return (int64_t)B * R * n <= (R == Hkv ? kStreamMaxTokensPerHead : kStreamMaxTokens);
+}
 
 // Per-row state of the streamed selection, caller-owned between steps, two
 // uint4: (threshold key, keys whose first digit reached the threshold's, n,

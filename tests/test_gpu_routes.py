@@ -23,6 +23,29 @@ def _gpu():
     yield
 
 
+def _step_launches(B, Hq, Hkv, n, rows="token", streamed=True, **kw):
+    """Launches of a (non-reset) step; the keys of one sequence serve the batch."""
+    import paper_2602_18750_amd as H
+    k = torch.randn((1, Hkv, n, 128), device=DEV).to(torch.bfloat16).expand(B, -1, -1, -1)
+    q = torch.randn((B, Hq, 128), device=DEV).to(torch.bfloat16)
+    R = 1 if rows == "token" else Hkv
+    s, st = H.new_importance(B, R, n, DEV), H.new_stream_state(B, R, DEV) if streamed else None
+    return len(kernel_grids(lambda: H.hill_step(q, k, k, s, n // 10, granularity=rows, stream_state=st, **kw)))
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,rows,refine", [
+    (1, 8, 8, 32768, "kvhead", False),     # 262144 tokens in rows of one KV head each
+    (8, 8, 8, 4097, "kvhead", True),       # one token per row more
+    (4, 8, 1, 65536, "token", False),      # a token row of the only KV head
+    (6, 16, 8, 32768, "token", False),     # 196608 tokens in rows that several KV heads walk
+    (7, 16, 8, 32768, "token", True),
+])
+def test_streamed_selection_limit(B, Hq, Hkv, n, rows, refine):
+    """A streamed step is scan, update, select and merge (so few heads need no
+    statistics launch); past the limits the refine pass is among them."""
+    assert _step_launches(B, Hq, Hkv, n, rows) == 4 + refine
+
+
 # The scans' grids are capped at what stays resident on the chip, a number of
 # each kernel's own, asked for once per process.
 SCAN_GRIDS = r"""
