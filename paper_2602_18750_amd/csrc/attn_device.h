@@ -49,10 +49,13 @@ struct AttnLds {
 // the fewest passes, the last one with its heads past G masked (they repeat
 // head G-1 and are not stored).  The rows are read once per pass: the emit
 // kernel of a 3 x 20K step with 7 heads per KV head takes 11.2 us in one masked
-// pass, 22.0 head by head; 2 x 32K with 5 heads 12.1 and 20.6.  Whether there
-// are masked heads is a compile-time choice (MASK): groups of 1, 2, 4 and
+// pass, 22.0 head by head; 2 x 32K with 5 heads 12.1 and 20.6.  Twelve heads take
+// three whole passes of four instead (16K tokens, four layers, two passes of
+// eight -> three of four: RAW 148.1 -> 147.3, int8 150.2 -> 149.2, 4K 167.8 ->
+// 160.5; twenty heads the other way, 180.9 and 184.0).  Whether there are masked
+// heads is a compile-time choice (MASK): groups of 1, 2, 4 and
 // multiples of 8 heads need no clamps and tests.
-inline int heads_per_pass(int G) { return G > 4 ? 8 : G > 2 ? 4 : G; }
+inline int heads_per_pass(int G) { return G == 12 ? 4 : G > 4 ? 8 : G > 2 ? 4 : G; }
 inline bool masked_pass(int G) { return G % heads_per_pass(G) != 0; }
 
 // This lane's 8 query elements of heads g*G+hc .. +GC (16-lane row layout).
