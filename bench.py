@@ -736,8 +736,7 @@ def _counter_rows(directory: str, counter: str, name_part: str, steady: bool = F
 
 
 STEP_SOURCES = [os.path.join(ROOT, "paper_2602_18750_amd", "csrc", f)
-                for f in ("update.hip", "topk.hip", "emit_logits.hip", "topk_device.h", "attn_device.h", "hill_device.h",
-                          "hill_internal.h")]
+                for f in ("update.hip", "topk.hip", "attn_device.h", "hill_device.h", "hill_internal.h")]
 STEP_COUNTERS_FILE = os.path.join(ROOT, "profiles", "step_kernels_counters.json")
 
 

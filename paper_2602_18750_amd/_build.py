@@ -27,8 +27,7 @@ HOSTSAN_FLAGS = ["-O1", "-g", "-fno-omit-frame-pointer"] + [
 # per-kernel registers, scratch and occupancy as the compiler reports them
 RESOURCES = os.path.join(BUILD_DIR, "kernel_resources.txt")
 
-SOURCES = ["hill_api.cpp", "score.hip", "update.hip", "sketch.hip", "topk.hip", "emit_logits.hip",
-           "emit_gather.hip", "row.hip", "attn.hip", "bkp.hip", "noalloc.hip", "tier.hip"]
+SOURCES = ["hill_api.cpp", "score.hip", "update.hip", "sketch.hip", "topk.hip", "row.hip", "attn.hip", "bkp.hip", "noalloc.hip", "tier.hip"]
 CALIB_SOURCES = ["calib.hip"]
 ARCH = os.environ.get("HILL_OFFLOAD_ARCH", "gfx950")
 

@@ -355,10 +355,6 @@ hipError_t launch_topk_emit_lists(const RefineArgs& r, int rows, hipStream_t st)
 // slots).  launch_merge_write then merges the partials into at.out and
 // writes the ordered indices.
 hipError_t launch_topk_emit_attn(const RefineArgs& r, const AttnArgs& at, int dtype, hipStream_t st, Stamp ts = {});
-hipError_t launch_emit_logits(const RefineArgs& r, const AttnArgs& at, int dtype, bool streamed, hipStream_t st,
-                              Stamp ts);
-hipError_t launch_emit_gather(const RefineArgs& r, const AttnArgs& at, int dtype, bool streamed, hipStream_t st,
-                              Stamp ts);
 hipError_t launch_merge_write(const RefineArgs& r, const AttnArgs& at, int32_t* idx, int rows, hipStream_t st,
                               Stamp ts = {});
 // Short rows end their step in one launch (row_attend in row.hip) after the

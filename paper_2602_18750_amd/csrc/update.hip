@@ -585,7 +585,7 @@ __global__ __launch_bounds__(256) void update_raw_groups_kernel(UpdateArgs a)
     }
     if (do_hist) {
         __syncthreads();
-        key_hist_flush<256>(kh, hist_part(a, b));
+        key_hist_flush<256>(kh, a.hist + (int64_t)b * kHistRow);
     }
 }
 
