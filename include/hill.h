@@ -188,8 +188,10 @@ HILL_API hill_status hill_step(const hill_desc* d, const void* q, const void* k,
  *
  * Short rows (at most 4096 tokens and 1024 selected ones; where the attention
  * gathers K too, i.e. for sketch or RAW scores, also at most 256 selected
- * tokens or at least 64 KV heads in the batch) need neither REFINE nor MERGE:
- * SELECT then counts the digits, selects, attends and writes the outputs.
+ * tokens or at least 64 KV heads in the batch) need no launches for REFINE and
+ * MERGE: SELECT then counts the digits, selects, attends and writes the
+ * outputs, and the events of the two stages are recorded as empty intervals
+ * before and after it.
  *
  * Each non-NULL start[i] / stop[i] is a caller-created hipEvent_t
  * (hipEventCreate, timing enabled) that stage i's launch stamps when it

@@ -247,6 +247,15 @@ Stamp stage(const hill_step_events& ev, int i)
     return Stamp{static_cast<hipEvent_t>(ev.start[i]), static_cast<hipEvent_t>(ev.stop[i])};
 }
 
+// Stamps a stage that another stage's launch has taken over: an empty interval
+// (nothing is enqueued without events).
+hipError_t stamp_empty(Stamp ts, hipStream_t st)
+{
+    if (ts.start)
+        if (hipError_t e = hipEventRecord(ts.start, st)) return e;
+    return ts.stop ? hipEventRecord(ts.stop, st) : hipSuccess;
+}
+
 template <typename T>
 T* at(void* ws, size_t off)
 {
@@ -585,7 +594,9 @@ hill_status run_step(const hill_desc* d, const void* q, const void* k, const voi
     }
     if (short_row) {
         r.state_out = state4;
+        if (!state4 || stream_reset) HIP_TRY(stamp_empty(stage(e, HILL_STAGE_REFINE), st));
         HIP_TRY(launch_row_attend(r, a, s.dtype, idx_out, st, stage(e, HILL_STAGE_SELECT)));
+        HIP_TRY(stamp_empty(stage(e, HILL_STAGE_MERGE), st));
         return HILL_OK;
     }
     if (state4 && !stream_reset) {   // no refine pass

@@ -128,6 +128,32 @@ def test_selection_alone(rows, n, ks):
     assert torch.equal(val, s.gather(-1, idx.long()))
 
 
+@pytest.mark.parametrize("streamed", [False, True])
+def test_every_stage_is_stamped(streamed):
+    """A short row's one launch takes REFINE and MERGE over: their events are
+    recorded too, as empty intervals in their places (REFINE not in a streamed
+    step, which has no such stage)."""
+    import paper_2602_18750_amd as H
+    q, k, v, _ = _inputs(1, 32, 8, 1000, torch.bfloat16, 3)
+    s, st = H.new_importance(1, 1, 1000, DEV), H.new_stream_state(1, 1, DEV) if streamed else None
+    stages, stream = H.hill.STAGES, torch.cuda.current_stream()
+    start = [torch.cuda.Event(enable_timing=True) for _ in stages]
+    stop = [torch.cuda.Event(enable_timing=True) for _ in stages]
+    first = torch.cuda.Event(enable_timing=True)
+    for e in start + stop + [first]:
+        e.record(stream)
+    torch.cuda.synchronize()
+    ev = H.HillStepEvents.of([e.cuda_event for e in start], [e.cuda_event for e in stop])
+    H.hill_step(q, k, v, s, 100, stream_state=st, events=ev)
+    torch.cuda.synchronize()
+    at = 0.0
+    for name in ["scan", "update"] + ([] if streamed else ["refine"]) + ["select", "merge"]:
+        i = stages.index(name)
+        a, b = first.elapsed_time(start[i]), first.elapsed_time(stop[i])
+        assert 0.0 < a and at <= a + 1e-3 and a <= b + 1e-3, (name, at, a, b)
+        at = b
+
+
 def test_streamed_sequence_grows_past_the_row_limit():
     """The bound that a short row's step writes serves the first longer row."""
     import paper_2602_18750_amd as H
