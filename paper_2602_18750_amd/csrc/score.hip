@@ -139,9 +139,10 @@ struct KeysF16 {
 // int32 (|sum| < 2^24) and scaled by 2^(e_q + e_k).
 template <int HEADS>
 struct QueryCasts {
-    int8_t q8[HEADS][kHeadDim];
+    alignas(16) int8_t q8[HEADS][kHeadDim];   // read as 16-byte words
     int eq[HEADS];
 };
+static_assert(sizeof(QueryCasts<4>) % 16 == 0 && alignof(QueryCasts<4>) == 16, "one per wave");
 using QueryLds = QueryCasts<kMaxGroup>;
 
 // The queries of a key-sketch scan: cast once per (b, g) into LDS.
@@ -1018,7 +1019,7 @@ __device__ __forceinline__ void compute_unit_tile(const ScoreArgs& a, int j0, in
 template <typename Keys, int HB>
 __global__ __launch_bounds__(256, 4) void score_units_kernel(ScoreArgs a)
 {
-    __shared__ float unit_lds[4][HB][kUnitTokens];
+    __shared__ __attribute__((aligned(16))) float unit_lds[4][HB][kUnitTokens];   // stored and read as float4
     __shared__ typename std::conditional<Keys::kCast, QueryCasts<HB>[4], int>::type q_lds;
     constexpr int kD = Keys::kDepth;
     static_assert(kUnitTiles % kD == 0 && kUnitTokens == 4 * 64, "slots repeat per unit; 16 bytes per lane and head");
