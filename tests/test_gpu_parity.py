@@ -120,6 +120,9 @@ TOPK_CASES = [
     ("grid", 2, 4097, 4097), ("equal", 2, 5000, 17), ("signed", 2, 3000, 1500), ("nan", 2, 2000, 1999),
     ("lognormal", 1, 32768, 3276), ("lognormal", 4, 131072, 6553), ("grid", 1, 65536, 13107),
     ("normal", 8, 8192, 1), ("lognormal", 16, 9000, 450), ("nan", 1, 300, 300),
+    # rows past 32768 tokens, which are selected chunk by chunk
+    ("nan", 2, 32769, 4000), ("nan", 1, 70001, 70001), ("signed", 2, 70001, 35000), ("equal", 2, 40000, 17),
+    ("normal", 2, 32769, 1), ("grid", 1, 33000, 33000), ("grid", 2, 70003, 7000),
 ]
 
 
@@ -220,11 +223,15 @@ def run_steps(x, k_sel, mode, gran, steps, check_every=1, where=""):
 
 @pytest.mark.parametrize("B,Hq,Hkv,n,k,dt,gran", [(2, 10, 2, 1001, 100, "bf16", "token"),
                                                    (1, 12, 1, 333, 40, "fp16", "kvhead"),
-                                                   (1, 7, 1, 35, 9, "bf16", "token")])
+                                                   (1, 7, 1, 35, 9, "bf16", "token"),
+                                                   (1, 10, 2, 4300, 430, "bf16", "token"),
+                                                   (1, 24, 2, 4200, 420, "fp16", "kvhead"),
+                                                   (1, 7, 1, 5000, 500, "bf16", "token")])
 def test_step_with_uneven_group_sizes(B, Hq, Hkv, n, k, dt, gran):
     """hill_step where the matrix-core scan leaves query columns empty (G = 5,
-    7) or takes two passes (G = 12); the select+attend kernel then takes the
-    scan's logits of those heads."""
+    7) or takes two passes (G = 12); the short rows' kernel and (past 4096
+    tokens) the select+attend kernel then take the scan's logits of those
+    heads."""
     say("uneven group", B, Hq, Hkv, n, k, dt, gran)
     x = W.make_random(B, Hq, Hkv, 128, n, dt, steps=3, seed=n + Hq)
     run_steps(x, k, "attn", gran, 3, where="G %d" % (Hq // Hkv))

@@ -61,6 +61,9 @@ PIN_TOPK_CASES = [
     ("nan", 2, 2000, 300, 7, 0),              # NaN / +inf around the pins
     ("lognormal", 3, 777, 50, 0, 49),
     ("lognormal", 4, 131072, 6553, 4, 1024),
+    ("grid", 1, 33001, 33001, 20000, 20000),  # past 32768 tokens, chunk by chunk
+    ("nan", 2, 40000, 300, 7, 0),
+    ("equal", 2, 50000, 100, 10, 90),
 ]
 
 

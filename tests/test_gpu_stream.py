@@ -95,6 +95,10 @@ STREAM_CASES = [
     (1, 32, 32, 4096, "fp16", "token", 4, 819, 0, 0),
     (2, 16, 4, 5000, "bf16", "token", 5, 500, 4, 64),
     (1, 4, 4, 129, "bf16", "token", 4, 13, 0, 0),
+    # rows of at most 4096 tokens end in one launch on both sides; these stream
+    (2, 8, 2, 4500, "fp16", "kvhead", 5, 450, 0, 0),
+    (1, 32, 32, 4200, "fp16", "token", 4, 840, 0, 0),
+    (1, 4, 4, 4097, "bf16", "token", 4, 410, 0, 0),
 ]
 
 
@@ -129,15 +133,16 @@ def test_streamed_after_outside_change_of_s(factor):
     _pair_run(x, [(5000, 500)] * 6, resets=1, mutate={3: lambda s: s.mul_(factor)})
 
 
-def test_streamed_heavy_ties():
+@pytest.mark.parametrize("n", [4096, 4600])   # a short row on both sides where at most 1024 are picked, and a streamed one
+def test_streamed_heavy_ties(n):
     """Keys drawn from 40 distinct rows: equal S values across thousands of
     tokens, so the threshold needs all three digits and the tie ranks."""
-    x = W.make_random(1, 8, 2, 128, 4096, "bf16", steps=4, seed=5)
+    x = W.make_random(1, 8, 2, 128, n, "bf16", steps=4, seed=5)
     g = torch.Generator().manual_seed(3)
-    pick = torch.randint(0, 40, (4096,), generator=g)
+    pick = torch.randint(0, 40, (n,), generator=g)
     x.k[:, :, :, :] = x.k[:, :, pick, :].clone()
     say("streamed heavy ties")
-    _pair_run(x, [(4096, 1000), (4096, 1000), (4096, 2047), (4096, 2047)])
+    _pair_run(x, [(n, 1000), (n, 1000), (n, 2047), (n, 2047)])
 
 
 def test_heavy_ties_over_more_than_256_chunks():
@@ -233,14 +238,17 @@ def test_streamed_reset_steps(sink, recent):
     _pair_run(x2, [(5000, 500), (5000, 2000), (5000, 500)], sink=sink, recent=recent, resets=1)
 
 
-def test_streamed_several_kv_heads_per_workgroup():
-    """Workload 4's shape (B 4, n 131072, GQA 32/8): the select+attend kernel
-    takes four KV heads per workgroup there; the streamed steps (a reset step,
-    then streamed ones, including a growing budget) equal hill_step's."""
-    n = 131072
-    x = W.make_random(4, 32, 8, 128, n, "bf16", steps=4, seed=404, device=DEV)
+@pytest.mark.parametrize("B,Hq,Hkv,n,k", [
+    (4, 32, 8, 131072, 6553),     # four KV heads; so many tokens select through the refine pass when streamed too
+    (2, 32, 32, 32768, 3276),     # two KV heads, the streamed selection
+])
+def test_streamed_several_kv_heads_per_workgroup(B, Hq, Hkv, n, k):
+    """Batches whose select+attend kernel takes several KV heads per workgroup;
+    the streamed steps (a reset step, then streamed ones, including a growing
+    budget) equal hill_step's."""
+    x = W.make_random(B, Hq, Hkv, 128, n, "bf16", steps=4, seed=404, device=DEV)
     say("streamed, several KV heads per workgroup")
-    _pair_run(x, [(n, 6553), (n, 6553), (n, 6600), (n, 6553)], resets=1)
+    _pair_run(x, [(n, k), (n, k), (n, k + 47), (n, k)], resets=1)
 
 
 def test_stage_events_stamp_the_stages_that_run():

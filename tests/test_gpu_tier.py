@@ -165,6 +165,59 @@ def test_tiered_steps_equal_the_all_hbm_sketch_step(gran, streamed, nbits):
     _check_placement(cache, k, v, n, "end")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,n,k,dt,gran,nbits", [
+    (2, 8, 8, 1500, 150, "bf16", "token", 8),       # 1 head per KV head
+    (1, 16, 8, 2048, 256, "fp16", "kvhead", 8),     # 2: the longest row of the smaller form
+    (3, 16, 4, 2049, 205, "bf16", "kvhead", 4),     # 4
+    (2, 14, 2, 4096, 256, "fp16", "token", 8),      # 7: one masked pass, the longest short row
+    (8, 72, 8, 3000, 300, "bf16", "token", 8),      # 9: two passes; a long list (64 KV heads)
+    (1, 18, 2, 700, 70, "fp16", "kvhead", 4),
+    (10, 32, 8, 2000, 1000, "fp16", "token", 4),
+])
+def test_short_tiered_steps(B, Hq, Hkv, n, k, dt, gran, nbits):
+    """Short rows, whose one launch gathers K and V from both pools by itself:
+    as the all-HBM sketch step, bit for bit, and the oracle's attention."""
+    say("short tiered steps", B, Hq, Hkv, n, k, dt, gran, nbits)
+    x = W.make_random(B, Hq, Hkv, 128, n, dt, steps=3, seed=n + k)
+    q, kk, v = x.q.to(DEV), x.k.to(DEV), x.v.to(DEV)
+    cache = H().TieredCache(kk, v, min(2 * k, n // 2), granularity=gran, bits=nbits)
+    R = cache.R
+    bstate = H().BkpState(B, R, n, DEV)
+    s_a, s_b = H().new_importance(B, R, n, DEV), H().new_importance(B, R, n, DEV)
+    for t in range(3):
+        i_a, o_a = H().hill_step(q[t], kk, v, s_a, k, granularity=gran, sketch=cache.sketch)
+        i_b, o_b = H().hill_step_tiered(q[t], cache, s_b, k, n_tokens=n)
+        torch.cuda.synchronize()
+        assert torch.equal(s_a, s_b) and torch.equal(i_a, i_b) and torch.equal(o_a, o_b), "step %d" % t
+        hot = (torch.gather(cache.loc.long(), 2, i_b.long()) >= 0).float().mean()
+        assert t == 0 or 0.0 < float(hot) < 1.0, "both pools hold selected rows"
+        own = O.sparse_attn(bits(x.q[t]), bits(x.k), bits(x.v), i_b.cpu().numpy(), dt, gran)
+        check_outputs(o_b.cpu().numpy(), own, "short tiered step %d" % t)
+        promote, demote, counts = H().bkp_update(bstate, i_b, n_tokens=n, n_recent=cache.capacity // 4,
+                                                 capacity=cache.capacity)
+        H().hill_tier_apply(cache, promote, demote, counts, n_tokens=n)
+    torch.cuda.synchronize()
+    assert int(cache.status.item()) == 0
+
+
+def test_tiered_sequence_grows_past_the_short_rows():
+    """Streamed tiered steps across the longest short row (4096 tokens)."""
+    x = W.make_random(1, 32, 8, 128, 4200, "bf16", steps=6, seed=77)
+    q, kk, v = x.q.to(DEV), x.k.to(DEV), x.v.to(DEV)
+    cache = H().TieredCache(kk, v, 1000)
+    bstate = H().BkpState(1, 1, 4200, DEV)
+    s_a, s_b = H().new_importance(1, 1, 4200, DEV), H().new_importance(1, 1, 4200, DEV)
+    st = H().new_stream_state(1, 1, DEV)
+    for t, n in enumerate([4094, 4095, 4096, 4097, 4100, 4200]):
+        i_a, o_a = H().hill_step(q[t], kk, v, s_a, 250, n_tokens=n, sketch=cache.sketch)
+        i_b, o_b = H().hill_step_tiered(q[t], cache, s_b, 250, n_tokens=n, stream_state=st, stream_reset=t == 0)
+        promote, demote, counts = H().bkp_update(bstate, i_b, n_tokens=n, n_recent=400, capacity=1000)
+        H().hill_tier_apply(cache, promote, demote, counts, n_tokens=n)
+        torch.cuda.synchronize()
+        assert torch.equal(s_a, s_b) and torch.equal(i_a, i_b) and torch.equal(o_a, o_b), "n %d" % n
+        assert int(cache.status.item()) == 0
+
+
 def test_tiered_steps_at_the_32k_workload():
     """The Llama-3-8B-shaped 32K layer (GQA 32/8, bf16, outlier keys, k 3276)
     with a hot pool of 2k tokens: eight streamed tiered steps (three reset

@@ -4,7 +4,7 @@ histogram in several parts, against the forms they replace.
 S of a batch (several chunks per workgroup) must equal, bit for bit, S of its
 sequences updated one by one (one chunk per workgroup); the step's selection
 must equal the standalone selection of the step's own S (which counts its own
-histogram in one part) and the streamed step's.  Shapes: the last workgroup
+histogram in one part) and that of a step with a stream state.  Shapes: the last workgroup
 with fewer chunks, a last chunk of one token, 1, 2 and 4 heads in flight per
 wave, 1 to 8 histogram parts, pinned tokens, RAW scores."""
 import pytest
@@ -33,6 +33,9 @@ def _gpu():
     (3, 28, 4, 20011, "kvhead", "attn", 4, 64),    # 7 heads per row: one in flight
     (2, 64, 8, 40000, "kvhead", "attn", 0, 0),     # 8 heads per row, the statistics launch
     (2, 32, 8, 20000, "token", "raw", 0, 64),      # RAW: one chunk per workgroup, one part
+    (2, 32, 8, 9001, "kvhead", "attn", 0, 0),      # several chunks under a streamed bound: 1 head in flight
+    (4, 64, 4, 9000, "kvhead", "attn", 4, 0),      # 2
+    (16, 16, 4, 9000, "token", "attn", 0, 64),
 ])
 def test_chunks_and_parts(B, Hq, Hkv, n, rows, mode, sink, recent):
     import paper_2602_18750_amd as H
@@ -56,7 +59,9 @@ def test_chunks_and_parts(B, Hq, Hkv, n, rows, mode, sink, recent):
     assert torch.equal(idx, top)
     if mode == "attn":
         st = H.new_stream_state(B, R, DEV)
-        for reset in (True, False):     # the bound from the refine pass, then the streamed selection
+        # the bound from the refine pass, then the streamed selection (calls of more than 196608 tokens, 262144
+        # in KV-head rows, take the refine pass again)
+        for reset in (True, False):
             i2, o2 = H.hill_step(q, k, v, s2, ks, stream_state=st, stream_reset=reset, **kw)
             if reset:
                 torch.cuda.synchronize()
