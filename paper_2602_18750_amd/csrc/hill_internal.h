@@ -294,7 +294,7 @@ hipError_t launch_softmax_stats(const float2* part, float2* stats, int bh, int n
 // blocks exceed the kUpdResident workgroups that run at once (4 per CU of 256),
 // then as many as keep the grid there, so that the statistics, the histogram's
 // clear and flush and the launch of a workgroup are paid once for several
-// chunks.  A pure function of the shape (the workspace layout depends on it).
+// chunks.  A pure function of the shape: two places of a step ask for it.
 constexpr int kUpdResident = 4 * 256;
 constexpr int kUpdMaxChunks = 16;
 inline int update_chunks_per_wg(int64_t blocks)
@@ -308,13 +308,18 @@ inline int update_chunks_per_wg(int64_t blocks)
 // ns per request one after another; past some workgroups per row they are
 // spread over several copies, which the refine pass adds.  update_attn at 1 x
 // 131K (1024 workgroups on a row) in us: one part 18.2, two 11.4, four 8.7,
-// eight 6.9; 1 x 32K (256) 8.6, 6.3, 5.0; 79 workgroups on a row: even.  The
-// refine pass's second round trip costs 0.2 us at most.  The copies take the
-// place of the row's list of selected tokens (4 bytes per token, written after
-// the refine pass): at most `room` of them.
+// eight 6.9; 1 x 32K (256) 8.6, 6.3, 5.0.  The refine pass's second round trip
+// costs 0.5 us, so up to 96 workgroups one part it is: two or four parts -> one,
+// whole steps: 3 x 8933 (70 workgroups) 34.6 -> 34.4, 3 x 20011 with 4 KV-head
+// rows (79; two layers) 90.0 -> 89.3; on the other side 1 x 14000 (110; four
+// layers) 114.7 and 115.2.  The copies take the place of the row's list of
+// selected tokens (4 bytes per token, written after the refine pass): at most
+// `room` of them.
 constexpr int kMaxHistParts = 8;
+constexpr int kOnePartWgs = 96;
 inline int hist_parts(int64_t wgs_per_row, int n)
 {
+    if (wgs_per_row <= kOnePartWgs) return 1;
     const int64_t room = (int64_t)n * sizeof(int32_t) / (kHistRow * sizeof(uint32_t));
     int r = 1;
     while (r < kMaxHistParts && 2 * r <= room && wgs_per_row > 32 * r) r *= 2;

@@ -24,8 +24,9 @@ def _gpu():
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,n,rows,mode,sink,recent", [
-    (1, 32, 8, 4097, "token", "attn", 0, 0),       # 33 workgroups: the first size with two parts wanted (no room)
-    (1, 32, 8, 8449, "token", "attn", 0, 0),       # room for two parts
+    (1, 32, 8, 4097, "token", "attn", 0, 0),       # 33 workgroups: one part
+    (1, 32, 8, 12288, "token", "attn", 0, 0),      # 96: the last size with one
+    (1, 32, 8, 12289, "token", "attn", 0, 0),      # 97: two (room for no more)
     (1, 32, 8, 16641, "token", "attn", 4, 64),     # four parts, a last chunk of one token
     (1, 16, 8, 33281, "token", "attn", 0, 0),      # eight parts, 2 heads in flight
     (9, 32, 8, 16385, "token", "attn", 0, 0),      # 129 chunks: two per workgroup, the last with one
