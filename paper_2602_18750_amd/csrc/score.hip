@@ -5,6 +5,8 @@
 //                (Sec. 4.4 raw inner product; Eq. 1).  ATTN keeps the logits
 //                and, per 256-token unit, a (max, sum of exp2) pair per head;
 //                RAW sums each head group per token.
+//  score_units   the same logits and pairs for long ATTN launches: every wave
+//                walks whole units.
 //
 // The importance update that consumes the logits is in update.hip.
 //
@@ -16,9 +18,11 @@
 // tokens j0 + 4*rg .. j0 + 4*rg + 3.  A workgroup unit is 8 wave-tiles (256
 // tokens; each wave takes two); the tiles' pairs are merged in LDS into one
 // pair per head.  Queries stay in registers while (b, g) stays the same.
-// Latency is hidden by occupancy (four workgroups per CU) rather than by
-// double-buffering, which costs more registers than it returns.  Partial dot
-// products are combined by three DPP adds.  ATTN logits with G >= 4 heads per
+// Latency is hidden by occupancy (four to six workgroups per CU) rather than by
+// double-buffering, which costs more registers than it returns there; it pays
+// in the shortest launches (KeysF16MfmaPair) and in launches long enough for
+// whole units per wave (score_units, below).  Partial dot products are combined
+// by three DPP adds.  ATTN logits with G >= 4 heads per
 // KV head take the dots on the matrix cores instead (KeysF16Mfma: the same
 // tiles, units and whole-line loads, a different lane-to-element map).
 #include <hip/hip_ext.h>
@@ -1172,11 +1176,14 @@ hipError_t launch_score_inst(const ScoreArgs& a, int ncu, hipStream_t st, Stamp 
             return launch_resident<score_tiles_kernel<1, OUT, KeysSketchMfma4<DT>>>(a, total, ncu, st, ts);
         if (a.k8 && a.kbits == 8 && a.G >= 4)
             return launch_resident<score_tiles_kernel<1, OUT, KeysSketchMfma8<DT>>>(a, total, ncu, st, ts);
-        // 16-bit keys, G >= 4: the dots on the matrix cores as well; with at most two units per CU both of
-        // a wave's tiles are requested at once (KeysF16MfmaPair; whole steps, one tile at a time -> both:
-        // 1 x 8K 25.7 -> 25.1 us per layer; 1 x 16K even, 1 x 32K 31.7 -> 32.2, longer ones within 1 %)
+        // 16-bit keys, G >= 4: the dots on the matrix cores as well; where every CU has at most one unit, or
+        // (nearly) every one two, both of a wave's tiles are requested at once (KeysF16MfmaPair).  Whole steps of
+        // eight layers, one tile at a time -> both: 160 units 173.2 -> 168.3 us, 256 205.4 -> 202.3, 480 231.8 ->
+        // 229.7, 512 205.5 -> 204.3 (streamed); between, where some CUs hold two and wait longer for them, 320 215.8
+        // -> 217.1, 384 222.8 -> 226.0, 448 225.8 -> 226.8; 1 x 32K (1024) 253.5 -> 257
         if (!a.k8 && a.G >= 4) {
-            if (total <= 2ll * ncu && buffer_reaches(a))
+            const bool pair = total <= ncu || (total > 7ll * ncu / 4 && total <= 2ll * ncu);
+            if (pair && buffer_reaches(a))
                 return launch_resident<score_tiles_kernel<1, OUT, KeysF16MfmaPair<DT>>>(a, total, ncu, st, ts);
             return launch_resident<score_tiles_kernel<1, OUT, KeysF16Mfma<DT>>>(a, total, ncu, st, ts);
         }
