@@ -1117,11 +1117,18 @@ int resident_per_cu()
 }
 
 // A persistent grid: at most `blocks` workgroups, every one resident at once.
+// over = 2: up to twice as many as are resident, one unit each.  Just past the
+// residency the persistent form gives half of its workgroups two units and the
+// others none; 16-bit tiles, persistent -> one unit each (us, two layers of MHA,
+// else one): MHA 1 x 8448 (1088 units, 1024 resident) 71.2 -> 67.8, 1 x 10K 73.7 ->
+// 72.6, 1 x 16K even; GQA 32/8 6 x 8200 (1632, 1536 resident) 45.6 -> 43.9, 9 x
+// 8000 (2304) 56.6 -> 54.1; RAW 6 x 8200 42.4 -> 41.1.  Sketch scans cast their
+// queries per workgroup and stay: int4 5 x 9500 36.6 -> 37.1.
 template <auto Kernel>
-hipError_t launch_resident(const ScoreArgs& a, int64_t blocks, int ncu, hipStream_t st, Stamp ts)
+hipError_t launch_resident(const ScoreArgs& a, int64_t blocks, int ncu, hipStream_t st, Stamp ts, int over = 1)
 {
     const int64_t cap = (int64_t)ncu * resident_per_cu<Kernel>();
-    const int64_t grid = blocks < cap ? (blocks < 1 ? 1 : blocks) : cap;
+    const int64_t grid = blocks < over * cap ? (blocks < 1 ? 1 : blocks) : cap;
     hipExtLaunchKernelGGL(Kernel, dim3((unsigned)grid), dim3(256), 0, st, ts.start, ts.stop, 0, a);
     return hipGetLastError();
 }
@@ -1185,13 +1192,13 @@ hipError_t launch_score_inst(const ScoreArgs& a, int ncu, hipStream_t st, Stamp 
             const bool pair = total <= ncu || (total > 7ll * ncu / 4 && total <= 2ll * ncu);
             if (pair && buffer_reaches(a))
                 return launch_resident<score_tiles_kernel<1, OUT, KeysF16MfmaPair<DT>>>(a, total, ncu, st, ts);
-            return launch_resident<score_tiles_kernel<1, OUT, KeysF16Mfma<DT>>>(a, total, ncu, st, ts);
+            return launch_resident<score_tiles_kernel<1, OUT, KeysF16Mfma<DT>>>(a, total, ncu, st, ts, 2);
         }
     }
     if (a.k8 && a.kbits == 4)
         return launch_resident<score_tiles_kernel<GC, OUT, KeysSketch<DT, GC, 4>>>(a, total, ncu, st, ts);
     if (a.k8) return launch_resident<score_tiles_kernel<GC, OUT, KeysSketch<DT, GC, 8>>>(a, total, ncu, st, ts);
-    return launch_resident<score_tiles_kernel<GC, OUT, KeysF16<DT, GC>>>(a, total, ncu, st, ts);
+    return launch_resident<score_tiles_kernel<GC, OUT, KeysF16<DT, GC>>>(a, total, ncu, st, ts, 2);
 }
 
 template <int DT, int OUT>

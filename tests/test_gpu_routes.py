@@ -23,6 +23,16 @@ def _gpu():
     yield
 
 
+@pytest.mark.parametrize("Hq,Hkv,n", [(32, 32, 8448), (32, 32, 9001)])   # 1088 and 1152 units, 1024 workgroups resident
+def test_scan_just_past_the_residency(Hq, Hkv, n):
+    """16-bit tiles: one unit per workgroup, not two for half of them."""
+    import paper_2602_18750_amd as H
+    k = torch.randn((1, Hkv, n, 128), device=DEV).to(torch.bfloat16)
+    q, s = torch.randn((1, Hq, 128), device=DEV).to(torch.bfloat16), H.new_importance(1, 1, n, DEV)
+    units = Hkv * 2 * ((n + 511) // 512)
+    assert kernel_grids(lambda: H.hill_score(q, k, s))[0][0] == units
+
+
 def _step_launches(B, Hq, Hkv, n, rows="token", streamed=True, **kw):
     """Launches of a (non-reset) step; the keys of one sequence serve the batch."""
     import paper_2602_18750_amd as H
