@@ -377,8 +377,17 @@ inline bool row_step(int B, int Hkv, int n, int k, bool kgather)
 {
     return n <= kRowTokens && k <= kRowPicks && (!kgather || k <= 256 || (int64_t)B * Hkv >= 64);
 }
-// The selection alone (row_topk) holds rows of up to kRowTopkTokens tokens: 2 x 16K in 13.7 us instead of five
-// launches of 18 and their boundaries.
+// A tiered cache's rows, partly in host memory, follow the same rule (us, half
+// to 95 % of the tokens in the hot pool): 1 x 2K 30.7 -> 27.4, 1 x 4K 32.5 ->
+// 29.8, 8 x 4K 153 -> 144 and 42.6 -> 41.1, 8 x 2K with 1000 picks 146 -> 139, 32 x
+// 4K 250 -> 240.
+//
+// The selection alone (row_topk) holds rows of up to kRowTopkTokens tokens: 2 x
+// 16K in 13.7 us instead of five launches of 18 and their boundaries.  Called as
+// a function with values, five launches -> one (us): one row of 4K 27.6 -> 11.6,
+// 16K 27.1 -> 12.8, 32K 27.0 -> 21.4; 32 rows of 32K 27.8 -> 23.5; 64 x 16K 28.0 ->
+// 14.6; 256 x 8K 39.5 -> 11.9, x 32K 109.7 -> 30.8; 512 x 4K 48.6 -> 17.6.  Longer rows
+// do not fit one workgroup's registers.
 constexpr int kRowTopkTokens = 32768;
 hipError_t launch_row_attend(const RefineArgs& r, const AttnArgs& at, int dtype, int32_t* idx, hipStream_t st,
                              Stamp ts = {});

@@ -429,8 +429,7 @@ __global__ __launch_bounds__(kUpdThreads) void update_attn_kernel(UpdateArgs a)
 // row blocks exceed what runs at once (update_chunks_per_wg): the statistics,
 // the histogram's clear and its flush are paid once, and the next chunk's
 // first HB logits per wave and S are loaded before this chunk is computed.
-// Measured, one chunk per workgroup -> this (us): 4 x 131K plain 36.8 -> 14.9,
-// streamed 18.9 -> 17.4; 32 x 32K 35 + 4.7 (the statistics launch) -> 26.4; 3
+// Measured, one chunk per workgroup -> this (us): 4 x 131K 36.8 -> 14.9; 32 x 32K 35 + 4.7 (the statistics launch) -> 26.4; 3
 // x 20K with 4 rows of 7 heads 14.2 -> 9.2 (the parts of the histogram
 // included).  For a single chunk the loop's bookkeeping costs 0.3-0.6 us.
 template <int HB>
